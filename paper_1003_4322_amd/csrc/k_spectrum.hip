@@ -55,86 +55,109 @@ int variant_count(const char* kind, int N, bool mhd) {
   return 1;
 }
 
-// Second stage: per-shell sums over planes in plane order, then the totals in
-// shell order, all Neumaier-compensated (one workgroup).  Q = 2 (energy):
-// spec[s] = E(s), totals = [sum E, sum Z, max over planes of pmax]; Q = 3
-// (MHD): spec[q nshell + s] = quantity q of shell s, totals[q] = its sum.
+// Second stage: per-shell sums over the plane pairs, then the totals over the
+// shells, all Neumaier-compensated and in a fixed order.  Q = 2 (energy):
+// spec[s] = E(s), totals = [sum E, sum Z, max of pmax]; Q = 3 (MHD):
+// spec[q nshell + s] = quantity q of shell s, totals[q] = its sum.
+constexpr int FIN_S = 32, FIN_G = 32;  // shells and plane groups of a workgroup
+
+// totals of the per-shell sums part[s Q + q] (one workgroup of FIN_S * FIN_G
+// threads): thread t adds shells t, t + 1024, ..., then a tree over the threads
 template <int Q>
-__global__ __launch_bounds__(1024) void k_spec_final(const double* part, const double* pmax, int nplanes,
-                                                     int nshell, double* spec, double* totals) {
-  __shared__ double sh[Q][1024];
-  NSum tot[Q];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) tot[q] = NSum{0, 0};
-  for (int s0 = 0; s0 < nshell; s0 += blockDim.x) {
-    const int s = s0 + threadIdx.x;
-    if (s < nshell) {
-      // planes in order; the loads of U planes are issued before their adds
-      constexpr int U = 8;
-      NSum e[Q];
-#pragma unroll
-      for (int q = 0; q < Q; ++q) e[q] = NSum{0, 0};
-      int p = 0;
-      for (; p + U <= nplanes; p += U) {
-        double v[U][Q];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int q = 0; q < Q; ++q) v[u][q] = part[((long)(p + u) * nshell + s) * Q + q];
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-          for (int q = 0; q < Q; ++q) nadd(e[q], v[u][q]);
-      }
-      for (; p < nplanes; ++p)
-#pragma unroll
-        for (int q = 0; q < Q; ++q) nadd(e[q], part[((long)p * nshell + s) * Q + q]);
-#pragma unroll
-      for (int q = 0; q < Q; ++q) {
-        const double v = e[q].s + e[q].c;
-        sh[q][threadIdx.x] = v;
-        if (Q == 3)
-          spec[q * nshell + s] = v;
-        else if (q == 0)
-          spec[s] = v;
-      }
+__device__ void spec_totals(const double* part, const double* pmax, int npm, int nshell, double* totals,
+                            double* red) {
+  const int t = threadIdx.x, nt = FIN_S * FIN_G;
+  for (int q = 0; q < 3; ++q) {
+    double v = 0;
+    if (q < Q) {
+      NSum sum{0, 0};
+      for (int s = t; s < nshell; s += nt) nadd(sum, part[(long)s * Q + q]);
+      v = sum.s + sum.c;
+    } else {
+      for (int i = t; i < npm; i += nt) v = fmax(v, pmax[i]);
     }
+    red[t] = v;
     __syncthreads();
-    if (threadIdx.x == 0) {
-      const int n = nshell - s0 < (int)blockDim.x ? nshell - s0 : (int)blockDim.x;
-      for (int i = 0; i < n; ++i)
-#pragma unroll
-        for (int q = 0; q < Q; ++q) nadd(tot[q], sh[q][i]);
+    for (int w = nt / 2; w > 0; w >>= 1) {
+      if (t < w) red[t] = q < Q ? red[t] + red[t + w] : fmax(red[t], red[t + w]);
+      __syncthreads();
     }
+    if (t == 0) totals[q] = red[0];
     __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int q = 0; q < Q; ++q) totals[q] = tot[q].s + tot[q].c;
-    if (Q == 2) {
-      double mx = 0;
-      for (int p = 0; p < nplanes; ++p) mx = fmax(mx, pmax[p]);
-      totals[2] = mx;
-    }
   }
 }
 
+// Workgroup b takes the shell blocks b, b + gridDim.x, ...; each thread adds
+// the planes g, g + FIN_G, ... of one shell, then the groups are added in
+// order.  The sums go to spec and (every q) to the first plane's place in part,
+// which only this workgroup has read; a launch of one workgroup also forms
+// the totals.
+template <int Q>
+__global__ __launch_bounds__(FIN_S* FIN_G) void k_spec_final(double* part, const double* pmax, int npm,
+                                                             int nplanes, int nshell, double* spec,
+                                                             double* totals) {
+  __shared__ double sh[Q][FIN_G][FIN_S];
+  const int l = threadIdx.x % FIN_S, g = threadIdx.x / FIN_S;
+  const int nblk = (nshell + FIN_S - 1) / FIN_S;
+  for (int b = blockIdx.x; b < nblk; b += gridDim.x) {
+    const int s = b * FIN_S + l;
+    NSum e[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) e[q] = NSum{0, 0};
+    if (s < nshell)
+      for (int p = g; p < nplanes; p += FIN_G)
+#pragma unroll
+        for (int q = 0; q < Q; ++q) nadd(e[q], part[((long)p * nshell + s) * Q + q]);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) sh[q][g][l] = e[q].s + e[q].c;
+    __syncthreads();
+    if (g < Q && s < nshell) {
+      NSum sum{0, 0};
+      for (int i = 0; i < FIN_G; ++i) nadd(sum, sh[g][i][l]);
+      const double v = sum.s + sum.c;
+      part[(long)s * Q + g] = v;
+      if (Q == 3 || g == 0) spec[g * nshell + s] = v;
+    }
+    __syncthreads();
+  }
+  if (gridDim.x == 1) spec_totals<Q>(part, pmax, npm, nshell, totals, &sh[0][0][0]);
+}
+template <int Q>
+__global__ __launch_bounds__(FIN_S* FIN_G) void k_spec_totals(const double* part, const double* pmax, int npm,
+                                                              int nshell, double* totals) {
+  __shared__ double red[FIN_S * FIN_G];
+  spec_totals<Q>(part, pmax, npm, nshell, totals, red);
+}
 
 template <typename T>
 hipError_t launch_spectrum(SpecArgs<T> a, bool mhd, double* spec, double* totals, hipStream_t s) {
-  // at most one 64-shell window per wave, at most SPEC_NF fields
-  if (a.nshell > 64 * SPEC_WAVES || (!mhd && a.nf > SPEC_NF)) return hipErrorInvalidValue;
+  const int nwin = spec_windows(a.nshell), nplanes = a.nz / 2 + 1, npm = nplanes * nwin;
+  // at most SPEC_MAXWIN windows (squares of 2 nshell stay below 2^24), at
+  // most SPEC_NF fields
+  if (nwin > SPEC_MAXWIN || a.nf > SPEC_NF) return hipErrorInvalidValue;
+  const dim3 grid(npm), block(SPEC_ROWS * 64);
   if (mhd)
-    k_spec_planes<T, true><<<dim3(a.nz), dim3(SPEC_WAVES * 64), 0, s>>>(a);
+    k_spec_planes<T, true, 6, true><<<grid, block, 0, s>>>(a);
+  else if (a.nf == 3)
+    k_spec_planes<T, false, 3, true><<<grid, block, 0, s>>>(a);
+  else if (a.nf == 6)
+    k_spec_planes<T, false, 6, true><<<grid, block, 0, s>>>(a);
   else
-    k_spec_planes<T, false><<<dim3(a.nz), dim3(SPEC_WAVES * 64), 0, s>>>(a);
+    k_spec_planes<T, false, 6, false><<<grid, block, 0, s>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (mhd)
-    k_spec_final<3><<<dim3(1), dim3(1024), 0, s>>>(a.part, a.pmax, a.nz, a.nshell, spec, totals);
-  else
-    k_spec_final<2><<<dim3(1), dim3(1024), 0, s>>>(a.part, a.pmax, a.nz, a.nshell, spec, totals);
-  return hipGetLastError();
+  // few partials: one workgroup adds them and the totals in one launch
+  const int nblk = (long)nplanes * a.nshell <= 8192 ? 1 : (a.nshell + FIN_S - 1) / FIN_S;
+  const dim3 fb(FIN_S * FIN_G);
+  auto finish = [&](auto q) -> hipError_t {
+    constexpr int Q = decltype(q)::value;
+    k_spec_final<Q><<<dim3(nblk), fb, 0, s>>>(a.part, a.pmax, npm, nplanes, a.nshell, spec, totals);
+    hipError_t er = hipGetLastError();
+    if (er != hipSuccess || nblk == 1) return er;
+    k_spec_totals<Q><<<dim3(1), fb, 0, s>>>(a.part, a.pmax, npm, a.nshell, totals);
+    return hipGetLastError();
+  };
+  return mhd ? finish(std::integral_constant<int, 3>{}) : finish(std::integral_constant<int, 2>{});
 }
 
 template hipError_t launch_spectrum<float>(SpecArgs<float>, bool, double*, double*, hipStream_t);

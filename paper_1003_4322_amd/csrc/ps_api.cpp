@@ -8,7 +8,8 @@
 //   zstar  F half spectra, dense pitch H = N/2+1       (RK2 midpoint state)
 //   work   2F half spectra, pitch P (H rounded up to 128 bytes)
 //          (physical-space passes: u, w [, b, j] and then the products)
-//   spec   N * nshell * 3 + N doubles                  (spectrum partials)
+//   spec   N * nshell * 3 + N doubles                  (spectrum partials; the
+//          N/2 + 1 plane pairs and their windows' maxima fit in it)
 // laid out [zstar of all boxes][work of all boxes][spec of all boxes].
 #include <hip/hip_runtime.h>
 
@@ -473,7 +474,7 @@ struct Seq {
   // six Elsasser fields (mhd true) of box i of the class
   ps_status spectrum(int i, const C* f, int nfl, bool mhd, double* spec, double* totals) {
     ps::SpecArgs<T> a{};
-    a.f = f; a.part = spec_part(i); a.pmax = a.part + (long)b.nz * b.nshell * (mhd ? 3 : 2);
+    a.f = f; a.part = spec_part(i); a.pmax = a.part + (long)(b.nz / 2 + 1) * b.nshell * (mhd ? 3 : 2);
     a.fs = b.nc; a.pitch = b.H; a.nx = b.nx; a.ny = b.ny; a.nz = b.nz; a.nf = nfl; a.nshell = b.nshell;
     a.sx = p->bs[0]; a.sy = p->bs[1]; a.sz = p->bs[2];
     return enqueue(p, s, "spectrum", nfl * b.nc * cs(),
@@ -1153,7 +1154,7 @@ ps_status ps_energy_spectrum_static(ps_plan p, const void* fhat, int nfields, do
         ps::SpecArgs<T> a{};
         a.f = (const ps::C2<T>*)fhat + b.cplx_off;
         a.part = p->scratch;
-        a.pmax = a.part + (long)b.nz * b.nshell * 2;
+        a.pmax = a.part + (long)(b.nz / 2 + 1) * b.nshell * 2;
         a.fs = c.nc; a.pitch = c.H; a.nx = b.nx; a.ny = b.ny; a.nz = b.nz; a.nf = nfields; a.nshell = b.nshell;
         a.sx = p->bs[0]; a.sy = p->bs[1]; a.sz = p->bs[2];
         const hipError_t e = ps::launch_spectrum<T>(a, false, spec_dev + so, totals_dev + 3 * i, p->stream);

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include "ps_kernels.hpp"
+#include "ps_spectrum.hpp"
 
 namespace ps {
 
