@@ -337,6 +337,8 @@ struct Seq {
   // fields of each stage: state, physical inputs of the products, products
   bool els(bool) const { return p->els; }
   int nphys(bool mhd) const { return p->els ? (mhd ? 6 : 3) : (mhd ? 12 : 6); }
+  // (kx, ky) columns the z passes transform in all boxes of the class
+  long columns() const { return (long)b.nb * (p->prune ? b.n_disk : (long)b.ny * b.H); }
   int nprod(bool mhd) const { return p->els ? (mhd ? 8 : 5) : (mhd ? 6 : 3); }
 
   ps_status pass_zcurl(const C* src, bool mhd) {
@@ -354,6 +356,9 @@ struct Seq {
     // at 512^3 FP64 0.82 -> 0.74 ms, FP32 unchanged)
     const double out_bytes = (double)nphys * nb * (p->prune ? (double)b.n_disk * b.nz : (double)b.nc) * cs();
     ca.nt = out_bytes > 268435456.0;
+    if (ps::z_curl_by_field(b.nz, columns()))
+      return enqueue(p, s, "z_curl", bytes,
+                     [&](hipStream_t q) { return ps::launch_z_curl_field<T>(b.nz, mhd, els(mhd), ca, b.dt, q); });
     return enqueue(p, s, "z_curl", bytes,
                    [&](hipStream_t q) { return ps::launch_z_curl<T>(b.nz, mhd, els(mhd), v, ca, b.dt, q); });
   }
@@ -392,6 +397,9 @@ struct Seq {
     if (p->prune)
       bytes = ((double)nprod * b.n_disk * b.nz +
                (mode == 0 ? (double)nst * b.nc : (double)(1 + nrw) * nst * b.n_sphere)) * nb * cs();
+    if (ps::z_epi_by_field(b.nz, columns()))
+      return enqueue(p, s, "z_epi", bytes,
+                     [&](hipStream_t q) { return ps::launch_z_epi_field<T>(b.nz, mhd, els(mhd), ea, b.dt, q); });
     return enqueue(p, s, "z_epi", bytes,
                    [&](hipStream_t q) { return ps::launch_z_epi<T>(b.nz, mhd, els(mhd), v, ea, b.dt, q); });
   }
@@ -546,29 +554,32 @@ ps_status upload_disk_tiles(ps_plan p, const Class& c) {
   if (p->dtiles.count(key)) return PS_OK;
   ps::DiskTiles& dt = p->dtiles[key];
   const bool mhd = p->nfields == 6;
-  std::set<int> widths;
+  std::set<int> widths{8, 16};  // the field-parallel passes
   for (int v = 0; v < ps::variant_count("z_curl", c.nz, mhd); ++v) widths.insert(ps::z_curl_tx<T>(c.nz, v));
   for (int v = 0; v < ps::variant_count("z_epi", c.nz, mhd); ++v) widths.insert(ps::z_epi_tx<T>(c.nz, v));
+  // all lists in one allocation and one copy
+  std::vector<int> all;
+  std::map<int, size_t> first;
   for (int tx : widths) {
     if (tx < 1 || tx > ps::DiskTiles::MAXTX) return fail(PS_ERR_STATE, "z-pass tile width out of range");
-    std::vector<int> list;
+    first[tx] = all.size();
     const long ntile = (c.H + tx - 1) / tx;
     for (long ky = 0; ky < c.ny; ++ky) {
       const int kyw = (int)(ky < c.ny / 2 ? ky : ky - c.ny);
       for (long t = 0; t < ntile; ++t)
-        if (c.g.disk((int)(t * tx), kyw)) list.push_back((int)(t | ky << 16));
+        if (c.g.disk((int)(t * tx), kyw)) all.push_back((int)(t | ky << 16));
     }
-    void* d = nullptr;
-    hipError_t e = hipMalloc(&d, std::max<size_t>(list.size(), 1) * sizeof(int));
-    if (e != hipSuccess) return fail(PS_ERR_NOMEM, std::string("disk tile list: ") + hipGetErrorString(e));
-    p->dbufs.push_back(d);
-    if (!list.empty()) {
-      e = hipMemcpy(d, list.data(), list.size() * sizeof(int), hipMemcpyHostToDevice);
-      if (e != hipSuccess) return hip_fail(e, "disk tile upload");
-    }
-    dt.list[tx] = (const int*)d;
-    dt.count[tx] = (int)list.size();
+    dt.count[tx] = (int)(all.size() - first[tx]);
   }
+  void* d = nullptr;
+  hipError_t e = hipMalloc(&d, std::max<size_t>(all.size(), 1) * sizeof(int));
+  if (e != hipSuccess) return fail(PS_ERR_NOMEM, std::string("disk tile list: ") + hipGetErrorString(e));
+  p->dbufs.push_back(d);
+  if (!all.empty()) {
+    e = hipMemcpy(d, all.data(), all.size() * sizeof(int), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "disk tile upload");
+  }
+  for (auto& f : first) dt.list[f.first] = (const int*)d + f.second;
   return PS_OK;
 }
 

@@ -436,6 +436,40 @@ __device__ __forceinline__ void fill_staged(C2<T>* dst, const C2<T>* tw, int twm
   for (int idx = tid; idx < L - 1; idx += nt) fill_staged_at<T, L, 1, Rs...>(dst, tw, twmul, idx);
 }
 
+// The staged twiddles of schedule RL (TwStaged) in two steps, so that their
+// loads and the data's are in flight together: load before the data's loads,
+// store after them.
+template <typename T, int L, int NT, class RL>
+struct TwFill {
+  static constexpr int E = cdiv(L - 1, NT);
+  C2<T> r[E];
+  template <int NS, int R, int... Rest>
+  __device__ __forceinline__ static int source(int idx, Radices<R, Rest...>) {
+    if (idx < NS * R - 1) {
+      const int o = idx - (NS - 1);
+      return (1 + o / NS) * (o % NS) * (L / (NS * R));
+    }
+    if constexpr (sizeof...(Rest) > 0)
+      return source<NS * R>(idx, Radices<Rest...>{});
+    else
+      return 0;
+  }
+  __device__ __forceinline__ void load(const C2<T>* tw, int tid) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int idx = tid + e * NT;
+      r[e] = idx < L - 1 ? tw[source<1>(idx, RL{})] : zero2<T>();
+    }
+  }
+  __device__ __forceinline__ void store(C2<T>* dst, int tid) const {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int idx = tid + e * NT;
+      if (idx < L - 1) dst[idx] = r[e];
+    }
+  }
+};
+
 // Exchange through LDS among the lanes of one wave.  A wave's LDS operations
 // complete in the order it issues them, so no s_barrier is needed; the
 // wavefront-scope fences and the wave barrier only keep the compiler from
@@ -448,9 +482,12 @@ __device__ __forceinline__ void wave_lds_sync() {
 
 // WAVE (the run_* template argument): every transform is done by lanes of a
 // single wave (the group of TQ threads lies in one wave) in an LDS buffer of
-// its own, so the exchanges after the first need only wave_lds_sync.  The
-// first stage's pre-write barrier stays a workgroup barrier, because a first
-// stage may gather from other transforms' buffers (a product of fields).
+// its own, so the exchanges after the first need only wave_lds_sync.  With
+// WAVE = 1 the first stage's pre-write barrier stays a workgroup barrier,
+// because a first stage may gather from other transforms' buffers (a product
+// of fields); WAVE = 2 makes it a wave_lds_sync too, for first stages that
+// read nothing another wave's transforms overwrite (no workgroup barrier is
+// left, so the waves of a workgroup may do different numbers of transforms).
 template <typename T, int L, int TQ, int DIR, class RL>
 struct Stockham {
   static constexpr int R1 = RadixInfo<RL>::first;
@@ -497,7 +534,7 @@ struct Stockham {
 
   // act = false: the thread only takes part in the barriers (its group has no
   // transform to do); v is left undefined
-  template <int NS, int R, bool FIRST, bool LAST, class Lay, bool WAVE, class TW, class Ld>
+  template <int NS, int R, bool FIRST, bool LAST, class Lay, int WAVE, class TW, class Ld>
   __device__ __forceinline__ static void stage(C2<T> (&v)[SLOTS], C2<T>* lds, int ls, int q, const TW& tw,
                                                Ld& ld, bool act) {
     constexpr int NB = cdiv(L / R, TQ);
@@ -541,7 +578,7 @@ struct Stockham {
     if constexpr (!LAST) {
       constexpr bool SPLIT_W = Lay::SPLIT == 2 || (Lay::SPLIT == 1 && (NS % 8 == 0 || (NS == 1 && R % 8 == 0)));
       // all reads of the previous LDS contents are done
-      if constexpr (WAVE && !FIRST)
+      if constexpr (WAVE == 2 || (WAVE == 1 && !FIRST))
         wave_lds_sync();
       else
         __syncthreads();
@@ -559,14 +596,14 @@ struct Stockham {
         }
       }
       // writes visible before the next stage gathers
-      if constexpr (WAVE)
+      if constexpr (WAVE != 0)
         wave_lds_sync();
       else
         __syncthreads();
     }
   }
 
-  template <int NS, class Lay, bool WAVE, class TW, class Ld, int R, int... Rest>
+  template <int NS, class Lay, int WAVE, class TW, class Ld, int R, int... Rest>
   __device__ __forceinline__ static void chain(C2<T> (&v)[SLOTS], C2<T>* lds, int ls, int q, const TW& tw,
                                                Ld& ld, bool act, Radices<R, Rest...>) {
     stage<NS, R, NS == 1, sizeof...(Rest) == 0, Lay, WAVE>(v, lds, ls, q, tw, ld, act);
@@ -576,7 +613,7 @@ struct Stockham {
   // ---- the same with a layout of its own per exchange (LayEx): stage
   // (NS, R) gathers through the layout of the exchange before it (LR) and
   // writes through LayEx<NS, R>.  One transform per buffer, unit stride.
-  template <int NS, int R, bool FIRST, bool LAST, class LR, bool WAVE, class TW, class Ld>
+  template <int NS, int R, bool FIRST, bool LAST, class LR, int WAVE, class TW, class Ld>
   __device__ __forceinline__ static void stage_ex(C2<T> (&v)[SLOTS], C2<T>* lds, int q, const TW& tw, Ld& ld,
                                                   bool act) {
     using LW = LayEx<NS, R, EXW>;
@@ -618,7 +655,7 @@ struct Stockham {
     }
     if constexpr (!LAST) {
       // all reads of the previous LDS contents are done
-      if constexpr (WAVE && !FIRST)
+      if constexpr (WAVE == 2 || (WAVE == 1 && !FIRST))
         wave_lds_sync();
       else
         __syncthreads();
@@ -633,23 +670,23 @@ struct Stockham {
         }
       }
       // writes visible before the next stage gathers
-      if constexpr (WAVE)
+      if constexpr (WAVE != 0)
         wave_lds_sync();
       else
         __syncthreads();
     }
   }
-  template <int NS, class LR, bool WAVE, class TW, class Ld, int R, int... Rest>
+  template <int NS, class LR, int WAVE, class TW, class Ld, int R, int... Rest>
   __device__ __forceinline__ static void chain_ex(C2<T> (&v)[SLOTS], C2<T>* lds, int q, const TW& tw, Ld& ld,
                                                   bool act, Radices<R, Rest...>) {
     stage_ex<NS, R, NS == 1, sizeof...(Rest) == 0, LR, WAVE>(v, lds, q, tw, ld, act);
     if constexpr (sizeof...(Rest) > 0)
       chain_ex<NS * R, LayEx<NS, R, EXW>, WAVE>(v, lds, q, tw, ld, act, Radices<Rest...>{});
   }
-  template <bool WAVE = false, class TW, class Ld>
+  template <int WAVE = 0, class TW, class Ld>
   __device__ __forceinline__ static void run_ex(C2<T> (&v)[SLOTS], C2<T>* lds, int q, const TW& tw, Ld ld,
                                                 bool act = true) {
-    static_assert(!WAVE || (TQ <= 64 && 64 % TQ == 0), "WAVE needs each transform inside one wave");
+    static_assert(WAVE != 1 || (TQ <= 64 && 64 % TQ == 0), "WAVE needs each transform inside one wave");
     chain_ex<1, LayEx<1, 1, EXW>, WAVE>(v, lds, q, tw, ld, act, RL{});
   }
   // LDS slots of one transform's buffer under run_ex (the exchanges, and the
@@ -676,13 +713,13 @@ struct Stockham {
   template <class Lay = LayStride, class Ld>
   __device__ __forceinline__ static void run(C2<T> (&v)[SLOTS], C2<T>* lds, int ls, int q,
                                              const C2<T>* __restrict__ tw, int twmul, Ld ld) {
-    chain<1, Lay, false>(v, lds, ls, q, TwTable<T>{tw, twmul}, ld, true, RL{});
+    chain<1, Lay, 0>(v, lds, ls, q, TwTable<T>{tw, twmul}, ld, true, RL{});
   }
   // any twiddle source (TwTable, TwStaged); act as in stage()
-  template <class Lay, bool WAVE = false, class TW, class Ld>
+  template <class Lay, int WAVE = 0, class TW, class Ld>
   __device__ __forceinline__ static void run_tw(C2<T> (&v)[SLOTS], C2<T>* lds, int ls, int q, const TW& tw,
                                                 Ld ld, bool act = true) {
-    static_assert(!WAVE || (TQ <= 64 && 64 % TQ == 0), "WAVE needs each transform inside one wave");
+    static_assert(WAVE != 1 || (TQ <= 64 && 64 % TQ == 0), "WAVE needs each transform inside one wave");
     chain<1, Lay, WAVE>(v, lds, ls, q, tw, ld, act, RL{});
   }
 };

@@ -28,6 +28,20 @@ struct DiskTiles {
   const int* list[MAXTX + 1] = {};
   int count[MAXTX + 1] = {};
 };
+// grid of a z pass: every tile, or only those in the disk list
+template <int TX>
+long z_grid(int ny, int ntile, int nb, bool listed, const DiskTiles* dt, const int*& tiles, int& ntl) {
+  static_assert(TX <= DiskTiles::MAXTX, "disk tile lists cover widths up to 16");
+  if (listed && dt && dt->list[TX]) {
+    tiles = dt->list[TX];
+    ntl = dt->count[TX];
+    return (long)ntl * nb;
+  }
+  tiles = nullptr;
+  ntl = 0;
+  return (long)ntile * ny * nb;
+}
+
 // tile width (columns per workgroup) of a z-pass variant
 template <typename T>
 int z_curl_tx(int N, int var);
@@ -49,6 +63,24 @@ template <typename T>
 hipError_t launch_x_r2c(int N, XArgs<T> a, hipStream_t s);
 template <typename T>
 hipError_t launch_x_prod(int N, bool mhd, bool els, int var, XArgs<T> a, hipStream_t s);
+// z passes with the fields of a column tile side by side, for launches whose
+// column tiles alone leave the chip idle; columns: those the pass transforms
+// in all boxes of the launch.  Measured, FP32 pruned / FP64 rotational unpruned
+// unless said (step times, us, one field after another against side by side):
+// the inverse pass gains up to 96 points and 32768 columns (MHD 32^3 FP64 114
+// to 90, NS 96^3 FP64 198 to 192, 16 boxes of 96^3 573 to 564) and loses beyond
+// (200 boxes of 32^3 FP64, 109 k columns, 1557 to 1596; NS 128^3 145 to 146);
+constexpr int ZCURL_FIELD_MAXN = 96;
+inline bool z_curl_by_field(int nz, long columns) { return nz <= ZCURL_FIELD_MAXN && columns <= 32768; }
+// the epilogue gains at every count up to 64 points (MHD 64^3 103 to 79; 48
+// boxes of 64^3 646 to 611) and up to 128 points while the columns are few
+// (NS 96^3 122 to 104, 1608 columns; NS 96^3 FP64, 4704 columns, 198 to 213; NS
+// 128^3 145 to 135, 2900 columns; unpruned, 8320 columns, 196 to 221).
+inline bool z_epi_by_field(int nz, long columns) { return nz <= 64 || (nz <= 128 && columns <= 4096); }
+template <typename T>
+hipError_t launch_z_curl_field(int N, bool mhd, bool els, ZCurlArgs<T> a, const DiskTiles* dt, hipStream_t s);
+template <typename T>
+hipError_t launch_z_epi_field(int N, bool mhd, bool els, ZEpiArgs<T> a, const DiskTiles* dt, hipStream_t s);
 // Bytes of the library-held device scratch of ps_energy_spectrum_static:
 // the partials of one box, nz * nshell * 2 + nz doubles (14.6 MB at
 // 1024^3, the largest supported grid).

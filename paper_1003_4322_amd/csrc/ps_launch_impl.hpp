@@ -83,20 +83,6 @@ constexpr int zepi_tx_of() {
   return StridedTX<T, N, ZepiSched<N, I>::TQ, ZEPI_V[I].sh>::value;
 }
 
-// grid of a z pass: every tile, or only those in the disk list
-template <int TX>
-long z_grid(int ny, int ntile, int nb, bool listed, const DiskTiles* dt, const int*& tiles, int& ntl) {
-  static_assert(TX <= DiskTiles::MAXTX, "disk tile lists cover widths up to 16");
-  if (listed && dt && dt->list[TX]) {
-    tiles = dt->list[TX];
-    ntl = dt->count[TX];
-    return (long)ntl * nb;
-  }
-  tiles = nullptr;
-  ntl = 0;
-  return (long)ntile * ny * nb;
-}
-
 template <typename T, int N, int I, bool MHD, bool ELS = false>
 hipError_t z_curl_v(ZCurlArgs<T> a, const DiskTiles* dt, hipStream_t s) {
   constexpr ZV v = ZCURL_V[I];
