@@ -379,6 +379,17 @@ struct Seq {
     return enqueue(p, s, "x_prod", (double)(nphys + nprod) * nb * per * cs(),
                    [&](hipStream_t q) { return ps::launch_x_prod<T>(b.nx, mhd, els(mhd), v, xa, q); });
   }
+  // the three passes of a plane's chain in one kernel
+  ps_status pass_plane(bool mhd, int z0, int nz) {
+    ps::PlaneArgs<T> a{};
+    a.work = work(); a.tw = twx();
+    a.fs = b.ncp; a.pitch = b.P; a.bs = wk_bs();
+    a.z0 = z0; a.nz = nz; a.nb = nb; a.g = b.g;
+    const double per = (double)nz * (p->prune ? (double)b.n_disk : (double)b.ny * b.H);
+    return enqueue(p, s, "yxy", (double)(nphys(mhd) + nprod(mhd)) * nb * per * cs(), [&](hipStream_t q) {
+      return ps::launch_plane<T>(b.nx, mhd, els(mhd), p->prune, (long)b.nz * b.nb > 256, a, q);
+    });
+  }
   ps_status pass_zepi(bool mhd, int mode, C* out, const C* st0, const C* st1, T h, T nua, T nub) {
     const int nprod = this->nprod(mhd), nst = mhd ? 6 : 3;
     ps::ZEpiArgs<T> ea{};
@@ -408,6 +419,7 @@ struct Seq {
   // inverse y, products, forward y on the z-planes [z0, z0 + nz): every plane's
   // chain is independent of the others' (only the z passes couple planes)
   ps_status yxy(bool mhd, int z0, int nz) {
+    if (ps::plane_fits<T>(b.nx, b.ny, mhd, els(mhd), p->prune)) return pass_plane(mhd, z0, nz);
     ps_status st = ypass(work(), b.P, wk_bs(), nphys(mhd), ps::INV, p->prune ? 1 : 0, z0, nz);
     if (!st) st = pass_xprod(mhd, z0, nz);
     if (!st) st = ypass(work(), b.P, wk_bs(), nprod(mhd), ps::FWD, p->prune ? 2 : 0, z0, nz);

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include "ps_kernels.hpp"
+#include "ps_plane.hpp"
 #include "ps_spectrum.hpp"
 
 namespace ps {
@@ -63,6 +64,13 @@ template <typename T>
 hipError_t launch_x_r2c(int N, XArgs<T> a, hipStream_t s);
 template <typename T>
 hipError_t launch_x_prod(int N, bool mhd, bool els, int var, XArgs<T> a, hipStream_t s);
+// Inverse y pass, products and forward y pass of whole z-planes in one kernel:
+// plane_fits says whether a (kx, ky) plane of the form's fields fits in LDS;
+// many: more planes in the class than the chip has CUs.
+template <typename T>
+bool plane_fits(int nx, int ny, bool mhd, bool els, bool prune);
+template <typename T>
+hipError_t launch_plane(int N, bool mhd, bool els, bool prune, bool many, PlaneArgs<T> a, hipStream_t s);
 // z passes with the fields of a column tile side by side, for launches whose
 // column tiles alone leave the chip idle; columns: those the pass transforms
 // in all boxes of the launch.  Measured, FP32 pruned / FP64 rotational unpruned
