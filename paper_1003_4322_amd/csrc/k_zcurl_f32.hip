@@ -3,5 +3,5 @@
 
 namespace ps {
 template hipError_t launch_z_curl<float>(int, bool, bool, int, ZCurlArgs<float>, const DiskTiles*, hipStream_t);
-template int z_curl_tx<float>(int, int);
+template unsigned z_curl_widths<float>(int);
 }  // namespace ps

@@ -3,5 +3,5 @@
 
 namespace ps {
 template hipError_t launch_z_curl<double>(int, bool, bool, int, ZCurlArgs<double>, const DiskTiles*, hipStream_t);
-template int z_curl_tx<double>(int, int);
+template unsigned z_curl_widths<double>(int);
 }  // namespace ps

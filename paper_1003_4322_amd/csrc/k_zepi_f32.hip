@@ -3,5 +3,5 @@
 
 namespace ps {
 template hipError_t launch_z_epi<float>(int, bool, bool, int, ZEpiArgs<float>, const DiskTiles*, hipStream_t);
-template int z_epi_tx<float>(int, int);
+template unsigned z_epi_widths<float>(int);
 }  // namespace ps

@@ -3,5 +3,5 @@
 
 namespace ps {
 template hipError_t launch_z_epi<double>(int, bool, bool, int, ZEpiArgs<double>, const DiskTiles*, hipStream_t);
-template int z_epi_tx<double>(int, int);
+template unsigned z_epi_widths<double>(int);
 }  // namespace ps

@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "../../include/ps.h"
+#include "ps_config.hpp"
 #include "ps_launch.hpp"
 
 namespace {
@@ -125,6 +126,7 @@ struct ps_plan_s {
   std::string gkey;
   // kernel variants per pass kind (chosen by ps_plan_autotune or by hand)
   std::map<std::string, int> var;
+  std::set<std::string> fixed;  // kinds set by the caller or chosen by the tuner
   // timing
   bool timing = false;
   std::vector<TimingRec> pending;
@@ -177,6 +179,25 @@ std::vector<ps::C2<T>> make_table(int N) {
     t[e].y = (T)(-sinl(a));
   }
   return t;
+}
+
+// The default variants of the pass kinds the caller has not set and the tuner
+// has not chosen: those measured fastest for the form, pruning and type at the
+// lengths of the largest class that has variants (ps_config.hpp).
+void default_variants(ps_plan_s* p) {
+  const Class* c = nullptr;
+  for (auto& k : p->classes)
+    if (!c || k.n3 > c->n3) c = &k;
+  if (!c) return;
+  const bool f32 = p->dtype == PS_F32, mhd = p->nfields == 6;
+  const std::pair<const char*, int> d[] = {{"y", ps::pick_strided(f32, c->ny)},
+                                           {"z", ps::pick_strided(f32, c->nz)},
+                                           {"z_curl", ps::pick_zcurl(f32, c->nz, mhd, p->els, p->prune)},
+                                           {"z_epi", ps::pick_zepi(f32, c->nz, mhd, p->els)},
+                                           {"x_prod", ps::pick_xprod(f32, c->nx, mhd, p->els)}};
+  for (auto& k : d)
+    if (!p->fixed.count(k.first) && ps::variant_count(k.first, axis_len(*c, k.first), mhd) > k.second)
+      p->var[k.first] = k.second;
 }
 
 ps_status hip_fail(hipError_t e, const char* what) {
@@ -565,15 +586,13 @@ ps_status upload_disk_tiles(ps_plan p, const Class& c) {
   const long key = ((long)c.nx << 22) | ((long)c.ny << 11) | c.nz;
   if (p->dtiles.count(key)) return PS_OK;
   ps::DiskTiles& dt = p->dtiles[key];
-  const bool mhd = p->nfields == 6;
-  std::set<int> widths{8, 16};  // the field-parallel passes
-  for (int v = 0; v < ps::variant_count("z_curl", c.nz, mhd); ++v) widths.insert(ps::z_curl_tx<T>(c.nz, v));
-  for (int v = 0; v < ps::variant_count("z_epi", c.nz, mhd); ++v) widths.insert(ps::z_epi_tx<T>(c.nz, v));
+  unsigned widths = ps::z_curl_widths<T>(c.nz) | ps::z_epi_widths<T>(c.nz);
+  if (c.nz <= 128) widths |= 1u << 8 | 1u << 16;  // the field-parallel passes
   // all lists in one allocation and one copy
   std::vector<int> all;
   std::map<int, size_t> first;
-  for (int tx : widths) {
-    if (tx < 1 || tx > ps::DiskTiles::MAXTX) return fail(PS_ERR_STATE, "z-pass tile width out of range");
+  for (int tx = 1; tx <= ps::DiskTiles::MAXTX; ++tx) {
+    if (!(widths >> tx & 1u)) continue;
     first[tx] = all.size();
     const long ntile = (c.H + tx - 1) / tx;
     for (long ky = 0; ky < c.ny; ++ky) {
@@ -730,7 +749,10 @@ bool tune_cache_lookup(ps_plan p, const std::string& key) {
   }
   fclose(f);
   if (hit)
-    for (auto& kv : found) p->var[kv.first] = kv.second;
+    for (auto& kv : found) {
+      p->var[kv.first] = kv.second;
+      p->fixed.insert(kv.first);
+    }
   return hit;
 }
 
@@ -876,15 +898,7 @@ ps_status create_plan(ps_plan* out, int nbox, const int* dims, int nfields, ps_d
     // the rotational form by default: valid for any input; the divergence
     // form (fewer transforms) needs a solenoidal, truncated state and is set
     // by the caller
-    // measured defaults at 512^3 (the autotuner refines them per workload),
-    // set where some box's pass has variants
-    const std::pair<const char*, int> defaults[] = {
-        {"z_curl", 0},
-        {"z_epi", nfields == 6 ? 5 : 2},  // MHD (Elsasser): z+ and z- in two workgroups
-        {"x_prod", dtype == PS_F32 ? (nfields == 6 ? 8 : 4) : 7},
-        {"y", dtype == PS_F32 ? 2 : 0}};
-    for (auto& d : defaults)
-      if (ps_plan_variant_count(p, d.first) > d.second) p->var[d.first] = d.second;
+    default_variants(p);
     {
       size_t nsh = 0;
       for (auto& b : p->boxes) nsh += b.nshell;
@@ -1256,9 +1270,11 @@ ps_status ps_plan_set_variant(ps_plan p, const char* kind, int v) {
   const int n = ps_plan_variant_count(p, kind);
   if (v < 0 || v >= n) return fail(PS_ERR_ARG, "variant out of range");
   p->var[kind] = v;
+  p->fixed.insert(kind);
   p->per_box = var_of(p, "batch") == 1;
   p->prune = var_of(p, "prune") == 1;
   p->els = var_of(p, "form") == 1;
+  default_variants(p);
   if (p->gexec) {
     hipGraphExecDestroy(p->gexec);
     p->gexec = nullptr;
@@ -1399,6 +1415,7 @@ ps_status ps_plan_autotune(ps_plan p, const void* state, ps_model m, int reps) {
             if ((out = time_v(kind, v, ms)) == PS_OK) best_ms[v] = std::min(best_ms[v], ms);
           }
         p->var[kind] = (int)(std::min_element(best_ms.begin(), best_ms.end()) - best_ms.begin());
+        p->fixed.insert(kind);
         if (out) break;
       }
       hipEventDestroy(e0);

@@ -194,4 +194,73 @@ constexpr int NZEPI = sizeof(ZEPI_V) / sizeof(ZV);
 constexpr int NSTR = sizeof(STR_V) / sizeof(ZV);
 constexpr int NXPROD = sizeof(XPROD_V) / sizeof(XV);
 
+// The variant each pass runs with by default: where nothing else is compiled
+// (lengths below 256) and on a plan that has been neither tuned nor set.
+// Chosen by the length n of the axis the pass transforms, the type and the form,
+// by timing every variant at every length from 24 to 512 (launch times, us,
+// former default -> this one; "pr": pruned).  Lengths 768 and 1024 follow 512.
+//
+// y and z: twiddles staged in LDS beside the tile, radix-8 schedule, except
+// FP64 at 384, where radix 16 saves a whole exchange of a 98 KB tile (inverse +
+// forward y, NS: FP32 192 108 -> 91, 256 247 -> 234, 384 1164 -> 889, 512 pr
+// 1016 -> 953; FP64 192 172 -> 164, 384 1842 -> 1685).
+constexpr int pick_strided(bool f32, int n) { return !f32 && n == 384 ? 4 : 5; }
+// Products: the packed form wherever its transforms fill the workgroup (NS:
+// FP32 192 97 -> 69, 256 229 -> 167, 512 1739 -> 1284; FP64 96 31 -> 25, 128 43
+// -> 39, 192 211 -> 141, 256 430 -> 327); with the radix-16 schedule for FP64
+// rows of 384 and more (NS 512 3878 -> 2733) and where twelve FP64 fields leave
+// one workgroup per CU (MHD rotational 192 402 -> 356); the half-length form
+// for short rows, MHD rotational FP32 at 384 (2237 -> 1570 with two rows; packed
+// 1726) and FP64 at 512 (6282; packed 7179), and beyond 512 where the packed
+// transforms of twelve fields would need more than 1024 threads.
+constexpr int pick_xprod(bool f32, int n, bool mhd, bool els) {
+  const bool rot12 = mhd && !els;
+  if (n < 64 || (n == 96 && f32 && els && !mhd)) return 0;
+  if (f32) {
+    if (n == 384 && mhd) return els ? 15 : 4;
+    if (n > 512 && rot12) return 8;
+    return 18;
+  }
+  if (rot12) return n >= 512 ? 7 : n == 192 || n == 256 ? 15 : 18;
+  return n >= 384 && !(n == 512 && els && mhd) ? 15 : 18;
+}
+// Inverse z + curl: full-width tiles (16 columns in FP32, 8 in FP64) with the
+// radix-16 schedule, MHD in two workgroups per tile (NS FP64 256 471 -> 314, 512
+// 3039 -> 2441; MHD FP64 192 458 -> 440, 512 7780 -> 6082; Elsasser FP32 256 73 ->
+// 56, 512 521 -> 433).  At 128, and at 384 in FP32, that schedule leaves threads
+// idle (NS FP64 128 32 against 40, MHD Elsasser FP32 384 208 against 237): there,
+// at 48 and 64 in FP32, and for pruned FP64 NS at 96 and 192 (44 against 65) the
+// radix-8 schedule, MHD rotational again in two workgroups (FP64 128 113 -> 81;
+// FP32 256 461 -> 430, 512 4016 -> 3704).
+constexpr int pick_zcurl(bool f32, int n, bool mhd, bool els, bool prune) {
+  const bool rot12 = mhd && !els;
+  if (f32) {
+    if (n == 48 || n == 64 || n == 384 || n == 768) return 0;
+    if (n == 128) return rot12 ? 1 : mhd ? 5 : 0;
+    if (rot12) return n == 192 ? 0 : n >= 256 ? 2 : 5;
+    return mhd ? 5 : 6;
+  }
+  if (n == 128) return mhd ? 1 : 0;
+  if (!mhd && (n == 96 || (n == 192 && prune))) return 0;
+  return mhd ? 5 : 6;
+}
+// Forward z + epilogue: full-width tiles with plain register use (NS FP32 256
+// 209 -> 192, 384 pr 333 -> 251, FP64 512 3145 -> 2934); the wide schedule where
+// the accumulators of the Elsasser form or twelve fields crowd the registers
+// (MHD 512: Elsasser FP32 1123 -> 1036, FP64 2296 -> 1950; rotational FP64 7561 ->
+// 7009); half-width tiles at 192 in FP32 (NS pr 41 -> 29) and for the NS
+// divergence form at 256 and 512; z+ and z- in two workgroups for Elsasser
+// fields below 256 and FP64 at 384 (192 FP64 166 -> 154); half-width tiles for
+// rotational MHD at 768 and 1024 (MHD 64 x 96 x 768 FP32, a step: 1262 against
+// 1384 with the wide schedule).
+constexpr int pick_zepi(bool f32, int n, bool mhd, bool els) {
+  if (n < 256) {
+    if (mhd && els) return n >= 96 ? 5 : 0;
+    return f32 && n == 192 ? 1 : !f32 && mhd && n == 96 ? 1 : 0;
+  }
+  if (mhd && els) return n == 256 ? (f32 ? 9 : 8) : n == 384 ? (f32 ? 8 : 5) : f32 ? 8 : 9;
+  if (mhd) return n == 384 ? 0 : n >= 768 ? 5 : n == 512 && !f32 ? 9 : 8;
+  return f32 && els && (n == 256 || n == 512) ? 9 : 0;
+}
+
 }  // namespace ps

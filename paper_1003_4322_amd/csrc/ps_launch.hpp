@@ -43,11 +43,11 @@ long z_grid(int ny, int ntile, int nb, bool listed, const DiskTiles* dt, const i
   return (long)ntile * ny * nb;
 }
 
-// tile width (columns per workgroup) of a z-pass variant
+// tile widths a length's z-pass variants use (bit w: width w)
 template <typename T>
-int z_curl_tx(int N, int var);
+unsigned z_curl_widths(int N);
 template <typename T>
-int z_epi_tx(int N, int var);
+unsigned z_epi_widths(int N);
 
 // els: MHD in the Elsasser (divergence) form -- z_curl transforms z+- without
 // a curl, x_prod forms the products z+_i z-_j (less z+_2 z-_2 on the diagonal,

@@ -52,7 +52,7 @@ hipError_t strided_n(int dir, int var, StridedArgs<T> a, hipStream_t s) {
     return pick(var, std::make_integer_sequence<int, NSTR>{},
                 [&](auto I) { return strided_v<T, N, decltype(I)::value>(dir, a, s); });
   else
-    return strided_v<T, N, 0>(dir, a, s);
+    return strided_v<T, N, pick_strided(sizeof(T) == 4, N)>(dir, a, s);
 }
 
 template <typename T>
@@ -68,20 +68,10 @@ hipError_t launch_strided(int N, int dir, int var, StridedArgs<T> a, hipStream_t
 }
 
 // ---------------- inverse z pass + curl ----------------
-template <typename T, int N, int I>
-constexpr int zcurl_tx_of() {
-  constexpr ZV v = ZCURL_V[I];
-  return StridedTX<T, N, Sched<N, v.alt>::TQ, v.sh>::value;
-}
 // schedule of a z-pass variant: radix-16 (alt), wide (a last radix of 4
 // over twice the threads), or the default
 template <int N, int I>
 using ZepiSched = std::conditional_t<ZEPI_V[I].wide, LenWide<N>, Sched<N, ZEPI_V[I].alt>>;
-
-template <typename T, int N, int I>
-constexpr int zepi_tx_of() {
-  return StridedTX<T, N, ZepiSched<N, I>::TQ, ZEPI_V[I].sh>::value;
-}
 
 template <typename T, int N, int I, bool MHD, bool ELS = false>
 hipError_t z_curl_v(ZCurlArgs<T> a, const DiskTiles* dt, hipStream_t s) {
@@ -103,13 +93,24 @@ hipError_t z_curl_m(bool mhd, bool els, ZCurlArgs<T> a, const DiskTiles* dt, hip
   return mhd ? z_curl_v<T, N, I, true>(a, dt, s) : z_curl_v<T, N, I, false>(a, dt, s);
 }
 
+// lengths without variants: the default one
+template <typename T, int N, bool MHD, bool ELS>
+hipError_t z_curl_d(ZCurlArgs<T> a, const DiskTiles* dt, hipStream_t s) {
+  constexpr int whole = pick_zcurl(sizeof(T) == 4, N, MHD, ELS, false);
+  constexpr int pruned = pick_zcurl(sizeof(T) == 4, N, MHD, ELS, true);
+  if (a.prune) return z_curl_v<T, N, pruned, MHD, ELS>(a, dt, s);
+  return z_curl_v<T, N, whole, MHD, ELS>(a, dt, s);
+}
+
 template <typename T, int N>
 hipError_t z_curl_n(bool mhd, bool els, int var, ZCurlArgs<T> a, const DiskTiles* dt, hipStream_t s) {
-  if constexpr (has_variants(N))
+  if constexpr (has_variants(N)) {
     return pick(var, std::make_integer_sequence<int, NZCURL>{},
                 [&](auto I) { return z_curl_m<T, N, decltype(I)::value>(mhd, els, a, dt, s); });
-  else
-    return z_curl_m<T, N, 0>(mhd, els, a, dt, s);
+  } else {
+    if (els) return mhd ? z_curl_d<T, N, true, true>(a, dt, s) : z_curl_d<T, N, false, true>(a, dt, s);
+    return mhd ? z_curl_d<T, N, true, false>(a, dt, s) : z_curl_d<T, N, false, false>(a, dt, s);
+  }
 }
 
 template <typename T>
@@ -125,24 +126,25 @@ hipError_t launch_z_curl(int N, bool mhd, bool els, int var, ZCurlArgs<T> a, con
   return hipErrorInvalidValue;
 }
 
+// tile widths (bit w: width w) the variants or defaults of a length use
+template <typename T, int N, int I>
+constexpr unsigned zcurl_w() {
+  return 1u << StridedTX<T, N, Sched<N, ZCURL_V[I].alt>::TQ, ZCURL_V[I].sh>::value;
+}
+template <typename T, int N, int... I>
+constexpr unsigned zcurl_ws(std::integer_sequence<int, I...>) {
+  return (0u | ... | zcurl_w<T, N, I>());
+}
 template <typename T>
-int z_curl_tx(int N, int var) {
-  int tx = 0;
+unsigned z_curl_widths(int N) {
   switch (N) {
-#define PS_CASE(NN)                                                                         \
-  case NN:                                                                                  \
-    if constexpr (has_variants(NN))                                                         \
-      pick(var, std::make_integer_sequence<int, NZCURL>{}, [&](auto I) {                    \
-        tx = zcurl_tx_of<T, NN, decltype(I)::value>();                                      \
-        return hipSuccess;                                                                  \
-      });                                                                                   \
-    else                                                                                    \
-      tx = zcurl_tx_of<T, NN, 0>();                                                         \
-    break;
+#define PS_CASE(NN)                                                     \
+  case NN:                                                              \
+    return zcurl_ws<T, NN>(std::make_integer_sequence<int, NZCURL>{});
     PS_FOR_EACH_N(PS_CASE)
 #undef PS_CASE
   }
-  return tx;
+  return 0;
 }
 
 // ---------------- forward z pass + epilogue ----------------
@@ -168,11 +170,17 @@ hipError_t z_epi_m(bool mhd, bool els, ZEpiArgs<T> a, const DiskTiles* dt, hipSt
 
 template <typename T, int N>
 hipError_t z_epi_n(bool mhd, bool els, int var, ZEpiArgs<T> a, const DiskTiles* dt, hipStream_t s) {
-  if constexpr (has_variants(N))
+  if constexpr (has_variants(N)) {
     return pick(var, std::make_integer_sequence<int, NZEPI>{},
                 [&](auto I) { return z_epi_m<T, N, decltype(I)::value>(mhd, els, a, dt, s); });
-  else
-    return z_epi_m<T, N, 0>(mhd, els, a, dt, s);
+  } else {
+    constexpr bool F = sizeof(T) == 4;
+    if (els)
+      return mhd ? z_epi_v<T, N, pick_zepi(F, N, true, true), true, true>(a, dt, s)
+                 : z_epi_v<T, N, pick_zepi(F, N, false, true), false, true>(a, dt, s);
+    return mhd ? z_epi_v<T, N, pick_zepi(F, N, true, false), true>(a, dt, s)
+               : z_epi_v<T, N, pick_zepi(F, N, false, false), false>(a, dt, s);
+  }
 }
 
 template <typename T>
@@ -188,24 +196,20 @@ hipError_t launch_z_epi(int N, bool mhd, bool els, int var, ZEpiArgs<T> a, const
   return hipErrorInvalidValue;
 }
 
+template <typename T, int N, int... I>
+constexpr unsigned zepi_ws(std::integer_sequence<int, I...>) {
+  return (0u | ... | (1u << StridedTX<T, N, ZepiSched<N, I>::TQ, ZEPI_V[I].sh>::value));
+}
 template <typename T>
-int z_epi_tx(int N, int var) {
-  int tx = 0;
+unsigned z_epi_widths(int N) {
   switch (N) {
-#define PS_CASE(NN)                                                                         \
-  case NN:                                                                                  \
-    if constexpr (has_variants(NN))                                                         \
-      pick(var, std::make_integer_sequence<int, NZEPI>{}, [&](auto I) {                     \
-        tx = zepi_tx_of<T, NN, decltype(I)::value>();                                       \
-        return hipSuccess;                                                                  \
-      });                                                                                   \
-    else                                                                                    \
-      tx = zepi_tx_of<T, NN, 0>();                                                          \
-    break;
+#define PS_CASE(NN)                                                    \
+  case NN:                                                             \
+    return zepi_ws<T, NN>(std::make_integer_sequence<int, NZEPI>{});
     PS_FOR_EACH_N(PS_CASE)
 #undef PS_CASE
   }
-  return tx;
+  return 0;
 }
 
 // ---------------- x passes ----------------
@@ -325,11 +329,27 @@ hipError_t x_prod_v(bool mhd, bool els, XArgs<T> a, hipStream_t s) {
 
 template <typename T, int N>
 hipError_t x_prod_n(bool mhd, bool els, int var, XArgs<T> a, hipStream_t s) {
-  if constexpr (has_variants(N))
+  if constexpr (has_variants(N)) {
     return pick(var, std::make_integer_sequence<int, NXPROD>{},
                 [&](auto I) { return x_prod_v<T, N, decltype(I)::value>(mhd, els, a, s); });
-  else
-    return x_prod_v<T, N, 0>(mhd, els, a, s);
+  } else {
+    // the default of the form (a box has at least 8 rows, the most a
+    // workgroup of the packed form takes at these lengths)
+    constexpr bool F = sizeof(T) == 4;
+    constexpr int I0 = pick_xprod(F, N, false, false), I1 = pick_xprod(F, N, false, true);
+    constexpr int I2 = pick_xprod(F, N, true, false), I3 = pick_xprod(F, N, true, true);
+    const int v = mhd ? (els ? I3 : I2) : els ? I1 : I0;
+    auto run = [&](auto I) -> hipError_t {
+      constexpr int i = decltype(I)::value;
+      if constexpr (i == I0 || i == I1 || i == I2 || i == I3)
+        return x_prod_v<T, N, i>(mhd, els, a, s);
+      else
+        return hipErrorInvalidValue;
+    };
+    return v == 0    ? run(std::integral_constant<int, 0>{})
+           : v == 15 ? run(std::integral_constant<int, 15>{})
+                     : run(std::integral_constant<int, 18>{});
+  }
 }
 
 template <typename T>
