@@ -947,6 +947,17 @@ __host__ __device__ constexpr unsigned xpk_mid_slots() {
   return z;
 }
 
+// Bound by vector issue and LDS, about equally, with memory close behind.  The
+// rows' loads go out with the twiddles' (a workgroup lives about 12 us, and used
+// to wait for the two one after the other), only the hand-overs between
+// transforms use workgroup barriers (three; seven before), the split takes Z[k]
+// from registers (five LDS writes and three reads fewer of 142 operations per
+// thread at 512), and the field is uniform over a wave.  Launch times, us, old
+// and new: MHD 512 FP32, 32 planes, 100 -> 87 (3.6 TB/s), FP64 183 -> 167; NS
+// 256^3 FP32 126 -> 115; NS 1024 FP32, 64 planes, 652 -> 595; NS 128^3 FP32 67 ->
+// 57; NS 512 rotational unpruned FP32 159 -> 146.  (Twiddles kept in registers
+// from the inverse to the forward transform cost occupancy: 95 and, at 1024,
+// 967 us; sixteen values per thread: 105 us at 512, 706 at 1024.)
 // EX: the Stockham exchanges use per-exchange layouts (LayEx, immediate
 // offsets) and rows are kept in natural order; otherwise every exchange and
 // row uses RLay.  PR: the input holds kx <= (N - 1) / 3 only (the launcher
@@ -969,10 +980,17 @@ __global__ __launch_bounds__(xpk_slots(MHD, ELS, RB) * TQ) void k_x_prod_pk(XArg
   __shared__ C2<T> smem[W * LP + N];
   C2<T>* tws = smem + W * LP;  // the transforms' twiddles, staged (TwStaged layout)
   const int tid = threadIdx.x, q = tid % TQ;
-  // the transform index is uniform over a wave when a transform spans whole
-  // waves: keep it in a scalar register (row pointers and product terms
-  // then cost scalar, not vector, instructions)
+  // The transform index c, the field it carries and the field's row pair.  All
+  // but the last are uniform over a wave when a transform spans whole waves;
+  // the field is, too, when a wave's transforms are row pairs of one field.
+  // Scalar registers then hold the row pointers' field part and the product
+  // terms (at 256 points, two transforms a wave, branches on a field known per
+  // lane only made 436 of the pass's 853 vector instructions).
+  constexpr int HB = RB / 2;  // row pairs per field
+  constexpr bool UNI = TQ % 64 != 0 && 64 % TQ == 0 && HB % (64 / TQ) == 0;
   const int c = TQ % 64 == 0 ? __builtin_amdgcn_readfirstlane(tid / TQ) : tid / TQ;
+  const int fld = UNI ? __builtin_amdgcn_readfirstlane(c / HB) : c / HB;
+  const int pr = c % HB;
   // grid rows of the workgroup: row0 + rb, rb < RB, in boxes of a.rows rows
   // (one division per workgroup; a.rows >= RB)
   const unsigned rows = (unsigned)a.rows, nrows = (unsigned)(a.rows * a.nb);
@@ -987,43 +1005,56 @@ __global__ __launch_bounds__(xpk_slots(MHD, ELS, RB) * TQ) void k_x_prod_pk(XArg
     }
     return row0 + rb < nrows;
   };
-  fill_staged<T, N>(tws, a.tw, 1, tid, NT, RL{});
-  __syncthreads();
-  const TwStaged<T> tw{tws};
   C2<T>* buf = smem + c * LP;
-  // row pointer of input real row r (field r / RB, grid row r % RB), or null
-  auto in_row = [&](int r) -> const C2<T>* {
+  TwFill<T, N, NT, RL> fill;
+  fill.load(a.tw, tid);
+  // row h of the pair of input field fld, or null
+  auto in_row = [&](int h) -> const C2<T>* {
     unsigned box, loc;
-    if (r >= FIN * RB || !row_of(r % RB, box, loc)) return nullptr;
-    return a.in + (long)box * a.in_bs + (long)(r / RB) * a.in_fs + (long)loc * a.in_pitch;
+    if (fld >= FIN || !row_of(2 * pr + h, box, loc)) return nullptr;
+    return a.in + (long)box * a.in_bs + (long)fld * a.in_fs + (long)loc * a.in_pitch;
   };
-  auto fft = [&](auto E, C2<T>(&v)[decltype(E)::SLOTS], auto ld, bool act) {
+  auto fft = [&](auto E, C2<T>(&v)[decltype(E)::SLOTS], const auto& tw, auto ld, bool act) {
     using EE = decltype(E);
     if constexpr (EX)
       EE::template run_ex<XW>(v, buf, q, tw, ld, act);
     else
       EE::template run_tw<RLay, XW>(v, buf, 1, q, tw, ld, act);
   };
-  // ---- inverse: Z = X + i Y from the stored half spectra, in the first stage
+  // a transform's exchanges are its own: where its threads lie in one wave no
+  // workgroup barrier is needed around them
+  auto own_sync = [] {
+    if constexpr (XW)
+      wave_lds_sync();
+    else
+      __syncthreads();
+  };
+  // ---- inverse: Z = X + i Y from the stored half spectra, in the first stage.
+  // The rows' loads and the twiddles' are in flight together; the first
+  // stage's barrier orders the staged twiddles before their first use.
   {
-    const C2<T>* sx = in_row(2 * c);
-    const C2<T>* sy = in_row(2 * c + 1);
-    const bool act = c < NI;
+    const C2<T>* sx = in_row(0);
+    const C2<T>* sy = in_row(1);
+    const bool act = fld < FIN;
+    C2<T> x[EI::FIRST_SLOTS], y[EI::FIRST_SLOTS];
+#pragma unroll
+    for (int s = 0; s < EI::FIRST_SLOTS; ++s) {
+      const int k = EI::first_index(q, s), kk = k > N / 2 ? N - k : k;  // stored index
+      const bool live = !((ZIN >> s) & 1u) && EI::first_valid(q, s) && kk <= a.kmax;
+      x[s] = sx && live ? sx[kk] : zero2<T>();
+      y[s] = sy && live ? sy[kk] : zero2<T>();
+    }
+    fill.store(tws, tid);
     C2<T> v[EI::SLOTS];
-    fft(EI{}, v,
-        ld_zero<ZIN>([&](int, int k) -> C2<T> {
-          const bool up = k > N / 2;
-          const int kk = up ? N - k : k;           // stored index
-          const bool real_bin = kk == 0 || 2 * kk == N;
-          const bool live = kk <= a.kmax;
-          C2<T> x = sx && live ? sx[kk] : zero2<T>();
-          C2<T> y = sy && live ? sy[kk] : zero2<T>();
-          const T xi = real_bin ? T(0) : (up ? -x.y : x.y);
-          const T yi = real_bin ? T(0) : (up ? -y.y : y.y);
-          return C2<T>{x.x - yi, xi + y.x};
+    fft(EI{}, v, TwStaged<T>{tws},
+        ld_zero<ZIN>([&](int s, int k) -> C2<T> {
+          const bool up = k > N / 2, real_bin = k == 0 || 2 * k == N;
+          const T xi = real_bin ? T(0) : (up ? -x[s].y : x[s].y);
+          const T yi = real_bin ? T(0) : (up ? -y[s].y : y[s].y);
+          return C2<T>{x[s].x - yi, xi + y[s].x};
         }),
         act);
-    __syncthreads();
+    own_sync();
     if (act) {
 #pragma unroll
       for (int s = 0; s < EI::LAST_NB * EI::RL_; ++s)
@@ -1032,51 +1063,36 @@ __global__ __launch_bounds__(xpk_slots(MHD, ELS, RB) * TQ) void k_x_prod_pk(XArg
   }
   __syncthreads();
   // ---- forward: products of the physical rows, two per transform.  With RB
-  // even, transform c carries product field fo on grid rows rb and rb + 1
-  // (rb = 2c mod RB), and input field f on those two rows sits in one slot as
-  // (x, y): each term of the pair is one component-wise product of two slots.
-  const bool fact = c < NO;
-  {
-    const int fo = (2 * c) / RB, rb2 = ((2 * c) % RB) / 2;
-    C2<T> v[EF::SLOTS];
-    fft(EF{}, v,
-        [&](int, int n) -> C2<T> {
-          C2<T> acc = zero2<T>();
-          if (2 * c >= FOUT * RB) return acc;
+  // even, a transform carries product field fld on grid rows 2 pr and 2 pr + 1,
+  // and input field f on those two rows sits in one slot as (x, y): each term
+  // of the pair is one component-wise product of two slots.
+  const bool fact = fld < FOUT;
+  C2<T> v[EF::SLOTS];
+  fft(EF{}, v, TwStaged<T>{tws},
+      [&](int, int n) -> C2<T> {
+        C2<T> acc = zero2<T>();
 #pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const PTerm pt = prod_def(MHD, ELS, fo).t[t];
-            if (pt.s != 0) {
-              const C2<T> x = smem[(pt.a * (RB / 2) + rb2) * LP + roff(n)];
-              const C2<T> y = smem[(pt.b * (RB / 2) + rb2) * LP + roff(n)];
-              acc = C2<T>{acc.x + T(pt.s) * x.x * y.x, acc.y + T(pt.s) * x.y * y.y};
-            }
+        for (int t = 0; t < 4; ++t) {
+          const PTerm pt = prod_def(MHD, ELS, fld).t[t];
+          if (pt.s != 0) {
+            const C2<T> x = smem[(pt.a * HB + pr) * LP + roff(n)];
+            const C2<T> y = smem[(pt.b * HB + pr) * LP + roff(n)];
+            acc = C2<T>{acc.x + T(pt.s) * x.x * y.x, acc.y + T(pt.s) * x.y * y.y};
           }
-          return acc;
-        },
-        fact);
-    __syncthreads();
-    if (fact) {
-#pragma unroll
-      for (int s = 0; s < EF::LAST_NB * EF::RL_; ++s)
-        if (!((ZOUT >> s) & 1u) && EF::last_valid(q, s)) buf[roff(EF::last_index(q, s))] = v[s];
-    }
-  }
-  __syncthreads();
-  if (!fact) return;
-  // ---- split the two spectra and store kx = 0 .. min(N/2, kmax)
+        }
+        return acc;
+      },
+      fact);
+  // ---- split the two spectra and store kx = 0 .. kend = min(N/2, kmax)
   const int kend = a.kmax < N / 2 ? a.kmax : N / 2;
   C2<T>* dst[2] = {nullptr, nullptr};
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const int p = 2 * c + h;
     unsigned box, loc;
-    if (p < FOUT * RB && row_of(p % RB, box, loc))
-      dst[h] = a.out + (long)box * a.out_bs + (long)(p / RB) * a.out_fs + (long)loc * a.out_pitch;
+    if (fact && row_of(2 * pr + h, box, loc))
+      dst[h] = a.out + (long)box * a.out_bs + (long)fld * a.out_fs + (long)loc * a.out_pitch;
   }
-  for (int k = q; k <= kend; k += TQ) {
-    const C2<T> zk = buf[roff(k)];
-    const C2<T> zm = conj(buf[roff(k == 0 ? 0 : N - k)]);
+  auto split = [&](int k, C2<T> zk, C2<T> zm) {  // Z[k] and conj Z[N - k]
     const C2<T> P = T(0.5) * (zk + zm);
     const C2<T> Q = T(0.5) * mul_mi(zk - zm);
     if (a.nt) {
@@ -1086,6 +1102,36 @@ __global__ __launch_bounds__(xpk_slots(MHD, ELS, RB) * TQ) void k_x_prod_pk(XArg
       if (dst[0]) dst[0][k] = P;
       if (dst[1]) dst[1][k] = Q;
     }
+  };
+  own_sync();
+  if constexpr ((N / EF::RL_) % TQ == 0) {
+    // the thread holds Z[q + TQ j], j < J: Z[k] comes from its registers, and
+    // only the upper half, Z[N - k], goes through LDS
+    constexpr int J = N / TQ, NB = EF::LAST_NB;
+    auto slot = [](int j) constexpr { return (j % NB) * EF::RL_ + j / NB; };
+    if (fact) {
+#pragma unroll
+      for (int j = J / 2; j < J; ++j)
+        if (TQ * (j + 1) > N - kend) buf[roff(q + TQ * j)] = v[slot(j)];
+    }
+    own_sync();
+    if (!fact) return;
+#pragma unroll
+    for (int j = 0; j <= J / 2; ++j) {
+      const int k = q + TQ * j;
+      if (k > kend) continue;
+      const C2<T> zk = v[slot(j)];
+      split(k, zk, conj(k == 0 ? zk : buf[roff(N - k)]));
+    }
+  } else {
+    if (fact) {
+#pragma unroll
+      for (int s = 0; s < EF::LAST_NB * EF::RL_; ++s)
+        if (!((ZOUT >> s) & 1u) && EF::last_valid(q, s)) buf[roff(EF::last_index(q, s))] = v[s];
+    }
+    own_sync();
+    if (!fact) return;
+    for (int k = q; k <= kend; k += TQ) split(k, buf[roff(k)], conj(buf[roff(k == 0 ? 0 : N - k)]));
   }
 }
 

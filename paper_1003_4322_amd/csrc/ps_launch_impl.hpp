@@ -243,9 +243,12 @@ hipError_t x_prod_pk_v(bool mhd, bool els, XArgs<T> a, hipStream_t s) {
   auto go = [&](auto mhd_c, auto els_c) -> hipError_t {
     constexpr bool M_ = decltype(mhd_c)::value, E_ = decltype(els_c)::value;
     constexpr int FI = xprod_fin(M_, E_), FO = xprod_fout(M_, E_);
-    // short transforms: enough rows per workgroup for about 256 threads
+    // short transforms: enough rows per workgroup for about 256 threads, and
+    // for the transforms of a wave to be row pairs of one field
     constexpr int want0 = M_ ? v.rb_mhd : v.rb_ns;
-    constexpr int wfill = 256 / (X::w(FI, FO, 1) * LC::TQ) > want0 ? 256 / (X::w(FI, FO, 1) * LC::TQ) : want0;
+    constexpr int uni = LC::TQ < 64 && 64 % LC::TQ == 0 ? 2 * (64 / LC::TQ) : 0;
+    constexpr int fill = 256 / (X::w(FI, FO, 1) * LC::TQ);
+    constexpr int wfill = fill > want0 ? (fill > uni ? fill : uni) : (want0 > uni ? want0 : uni);
     constexpr int RB = X::rb(FI, FO, wfill, LP, LIM);
     if constexpr (!X::fits(FI, FO, RB, LP, 163840)) {
       return hipErrorInvalidValue;
@@ -333,15 +336,16 @@ hipError_t x_prod_n(bool mhd, bool els, int var, XArgs<T> a, hipStream_t s) {
     return pick(var, std::make_integer_sequence<int, NXPROD>{},
                 [&](auto I) { return x_prod_v<T, N, decltype(I)::value>(mhd, els, a, s); });
   } else {
-    // the default of the form (a box has at least 8 rows, the most a
-    // workgroup of the packed form takes at these lengths)
+    // the default of the form; a launch of fewer rows than a workgroup of the
+    // packed form may take (8-row slabs of rows of 64 points) runs the
+    // half-length one
     constexpr bool F = sizeof(T) == 4;
     constexpr int I0 = pick_xprod(F, N, false, false), I1 = pick_xprod(F, N, false, true);
     constexpr int I2 = pick_xprod(F, N, true, false), I3 = pick_xprod(F, N, true, true);
-    const int v = mhd ? (els ? I3 : I2) : els ? I1 : I0;
+    const int v = a.rows < 16 ? 0 : mhd ? (els ? I3 : I2) : els ? I1 : I0;
     auto run = [&](auto I) -> hipError_t {
       constexpr int i = decltype(I)::value;
-      if constexpr (i == I0 || i == I1 || i == I2 || i == I3)
+      if constexpr (i == 0 || i == I0 || i == I1 || i == I2 || i == I3)
         return x_prod_v<T, N, i>(mhd, els, a, s);
       else
         return hipErrorInvalidValue;
