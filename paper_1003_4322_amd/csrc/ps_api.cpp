@@ -327,14 +327,30 @@ struct Seq {
                    [&](hipStream_t st) { return ps::launch_strided<T>(b.nz, dir, v, a, st); });
   }
 
-  ps_status r2c(const T* real_in, C* out) {
-    ps::XArgs<T> a{};
-    a.in = (const C*)real_in; a.out = out; a.tw = twx();
-    a.in_pitch = b.nx / 2; a.in_fs = (long)b.nz * b.ny * (b.nx / 2); a.in_bs = nf() * a.in_fs;
-    a.out_pitch = b.H; a.out_fs = b.nc; a.out_bs = st_bs();
-    a.rows = (long)b.ny * b.nz; a.nf = nf(); a.nb = nb;
+  // x and y passes of the plain transforms in one kernel (planes that fit in LDS)
+  ps_status planefft(int dir, T* real, C* cplx, long fs, long pitch, long bs) {
+    ps::PlaneFftArgs<T> a{};
+    a.tw = twx(); a.cplx = cplx; a.real = real; a.fs = fs; a.pitch = pitch; a.bs = bs;
+    a.nz = b.nz; a.nf = nf(); a.nb = nb;
     const double bytes = nf() * nb * (b.n3 * (double)sizeof(T) + b.nc * cs());
-    ps_status st = enqueue(p, s, "x_r2c", bytes, [&](hipStream_t q) { return ps::launch_x_r2c<T>(b.nx, a, q); });
+    return enqueue(p, s, dir == ps::FWD ? "xy_r2c" : "xy_c2r", bytes,
+                   [&](hipStream_t q) { return ps::launch_planefft<T>(b.nx, dir, a, q); });
+  }
+  ps_status xfft(int dir, T* real, C* cplx, long fs, long pitch, long bs) {
+    ps::XFftArgs<T> a{};
+    a.tw = twx(); a.cplx = cplx; a.real = real; a.fs = fs; a.pitch = pitch; a.bs = bs;
+    a.pairs = (unsigned)((long)b.ny * b.nz / 2); a.nf = nf(); a.nb = nb;
+    const double bytes = nf() * nb * (b.n3 * (double)sizeof(T) + b.nc * cs());
+    return enqueue(p, s, dir == ps::FWD ? "x_r2c" : "x_c2r", bytes,
+                   [&](hipStream_t q) { return ps::launch_xfft<T>(b.nx, dir, a, q); });
+  }
+  // (a forward transform only reads the real rows)
+  ps_status r2c(const T* real_in, C* out) {
+    if (ps::planefft_fits<T>(b.nx, b.ny)) {
+      ps_status st = planefft(ps::FWD, const_cast<T*>(real_in), out, b.nc, b.H, st_bs());
+      return st ? st : zpass(out, b.H, st_bs(), out, b.H, st_bs(), ps::FWD);
+    }
+    ps_status st = xfft(ps::FWD, const_cast<T*>(real_in), out, b.nc, b.H, st_bs());
     if (st) return st;
     if ((st = ypass(out, b.H, st_bs(), nf(), ps::FWD))) return st;
     return zpass(out, b.H, st_bs(), out, b.H, st_bs(), ps::FWD);
@@ -344,14 +360,9 @@ struct Seq {
     C* w = work();
     ps_status st = zpass(in, b.H, st_bs(), w, b.P, wk_bs(), ps::INV);
     if (st) return st;
+    if (ps::planefft_fits<T>(b.nx, b.ny)) return planefft(ps::INV, real_out, w, b.ncp, b.P, wk_bs());
     if ((st = ypass(w, b.P, wk_bs(), nf(), ps::INV))) return st;
-    ps::XArgs<T> a{};
-    a.in = w; a.out = (C*)real_out; a.tw = twx();
-    a.in_pitch = b.P; a.in_fs = b.ncp; a.in_bs = wk_bs();
-    a.out_pitch = b.nx / 2; a.out_fs = (long)b.nz * b.ny * (b.nx / 2); a.out_bs = nf() * a.out_fs;
-    a.rows = (long)b.ny * b.nz; a.nf = nf(); a.nb = nb;
-    const double bytes = nf() * nb * (b.n3 * (double)sizeof(T) + b.nc * cs());
-    return enqueue(p, s, "x_c2r", bytes, [&](hipStream_t q) { return ps::launch_x_c2r<T>(b.nx, a, q); });
+    return xfft(ps::INV, real_out, w, b.ncp, b.P, wk_bs());
   }
 
   // the five passes of one right-hand side evaluation

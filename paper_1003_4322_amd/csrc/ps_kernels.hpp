@@ -659,72 +659,6 @@ struct XArgs {
   int nt;    // fused pass: streaming stores for the output (set when it far exceeds the caches)
 };
 
-// plain inverse: complex rows (pitch in_pitch) -> real rows (N reals, pitch out_pitch complex = M)
-template <typename T, int M, int TQ, int G, class RL>
-__global__ __launch_bounds__(G* TQ) void k_x_c2r(XArgs<T> a) {
-  using E = Stockham<T, M, TQ, INV, RL>;
-  constexpr int LP = row_slots(M);
-  __shared__ C2<T> smem[G * LP];
-  const int tid = threadIdx.x, g = tid / TQ, q = tid % TQ;
-  const long row0 = (long)xcd_remap(blockIdx.x, gridDim.x) * G;
-  const long total = a.rows * a.nf * a.nb;
-  for (int i = tid; i < G * (M + 1); i += G * TQ) {
-    const int gg = i / (M + 1), k = i % (M + 1);
-    const long row = row0 + gg;
-    C2<T> val = zero2<T>();
-    if (row < total) {
-      const long fb = row / a.rows, r = row % a.rows;
-      const long f = fb % a.nf, b = fb / a.nf;
-      val = a.in[b * a.in_bs + f * a.in_fs + r * a.in_pitch + k];
-    }
-    smem[gg * LP + pad8(k)] = val;
-  }
-  __syncthreads();
-  C2<T>* buf = smem + g * LP;
-  C2<T> v[E::SLOTS];
-  E::template run<LayPad8>(v, buf, 1, q, a.tw, 2, [&](int, int k) { return c2r_pre(buf, k, M, a.tw); });
-  const long row = row0 + g;
-  if (row >= total) return;
-  const long fb = row / a.rows, r = row % a.rows;
-  const long f = fb % a.nf, b = fb / a.nf;
-  C2<T>* out = a.out + b * a.out_bs + f * a.out_fs + r * a.out_pitch;
-#pragma unroll
-  for (int s = 0; s < E::LAST_NB * E::RL_; ++s)
-    if (E::last_valid(q, s)) out[E::last_index(q, s)] = v[s];
-}
-
-// plain forward: real rows (as M complex, pitch in_pitch) -> complex rows (M+1, pitch out_pitch)
-template <typename T, int M, int TQ, int G, class RL>
-__global__ __launch_bounds__(G* TQ) void k_x_r2c(XArgs<T> a) {
-  using E = Stockham<T, M, TQ, FWD, RL>;
-  constexpr int LP = row_slots(M);
-  __shared__ C2<T> smem[G * LP];
-  const int tid = threadIdx.x, g = tid / TQ, q = tid % TQ;
-  const long row0 = (long)xcd_remap(blockIdx.x, gridDim.x) * G;
-  const long total = a.rows * a.nf * a.nb;
-  const long row = row0 + g;
-  const bool ok = row < total;
-  const long fb = ok ? row / a.rows : 0, r = ok ? row % a.rows : 0;
-  const C2<T>* in = a.in + (fb / a.nf) * a.in_bs + (fb % a.nf) * a.in_fs + r * a.in_pitch;
-  C2<T>* buf = smem + g * LP;
-  C2<T> v[E::SLOTS];
-  E::template run<LayPad8>(v, buf, 1, q, a.tw, 2, [&](int, int n) { return ok ? in[n] : zero2<T>(); });
-  __syncthreads();
-#pragma unroll
-  for (int s = 0; s < E::LAST_NB * E::RL_; ++s)
-    if (E::last_valid(q, s)) buf[pad8(E::last_index(q, s))] = v[s];
-  __syncthreads();
-  for (int i = tid; i < G * (M + 1); i += G * TQ) {
-    const int gg = i / (M + 1), k = i % (M + 1);
-    const long rw = row0 + gg;
-    if (rw < total) {
-      const long fb = rw / a.rows, rr = rw % a.rows;
-      a.out[(fb / a.nf) * a.out_bs + (fb % a.nf) * a.out_fs + rr * a.out_pitch + k] =
-          r2c_post(smem + gg * LP, k, M, a.tw);
-    }
-  }
-}
-
 // fused: FIN complex input fields -> inverse real FFTs -> cross products ->
 // forward real FFTs -> FOUT complex output fields.  RB rows per workgroup.
 // NS : in [u0 u1 u2 w0 w1 w2]             out [u x w]

@@ -8,6 +8,8 @@
 
 #include "ps_kernels.hpp"
 #include "ps_plane.hpp"
+#include "ps_planefft.hpp"
+#include "ps_xfft.hpp"
 #include "ps_spectrum.hpp"
 
 namespace ps {
@@ -59,10 +61,6 @@ template <typename T>
 hipError_t launch_z_epi(int N, bool mhd, bool els, int var, ZEpiArgs<T> a, const DiskTiles* dt,
                         hipStream_t s);
 template <typename T>
-hipError_t launch_x_c2r(int N, XArgs<T> a, hipStream_t s);
-template <typename T>
-hipError_t launch_x_r2c(int N, XArgs<T> a, hipStream_t s);
-template <typename T>
 hipError_t launch_x_prod(int N, bool mhd, bool els, int var, XArgs<T> a, hipStream_t s);
 // Inverse y pass, products and forward y pass of whole z-planes in one kernel:
 // plane_fits says whether a (kx, ky) plane of the form's fields fits in LDS;
@@ -89,6 +87,15 @@ template <typename T>
 hipError_t launch_z_curl_field(int N, bool mhd, bool els, ZCurlArgs<T> a, const DiskTiles* dt, hipStream_t s);
 template <typename T>
 hipError_t launch_z_epi_field(int N, bool mhd, bool els, ZEpiArgs<T> a, const DiskTiles* dt, hipStream_t s);
+// x and y passes of the plain transforms (dir FWD: r2c, INV: c2r) in one kernel,
+// where one field's plane fits in LDS
+template <typename T>
+bool planefft_fits(int nx, int ny);
+template <typename T>
+hipError_t launch_planefft(int N, int dir, PlaneFftArgs<T> a, hipStream_t s);
+// the x pass alone
+template <typename T>
+hipError_t launch_xfft(int N, int dir, XFftArgs<T> a, hipStream_t s);
 // Bytes of the library-held device scratch of ps_energy_spectrum_static:
 // the partials of one box, nz * nshell * 2 + nz doubles (14.6 MB at
 // 1024^3, the largest supported grid).

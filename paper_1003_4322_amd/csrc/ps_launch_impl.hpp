@@ -213,24 +213,6 @@ unsigned z_epi_widths(int N) {
 }
 
 // ---------------- x passes ----------------
-template <typename T, int N>
-hipError_t x_c2r_n(XArgs<T> a, hipStream_t s) {
-  using LC = LenCfg<N / 2>;
-  using X = XCfg<T, N / 2, LC::TQ>;
-  const long grid = (a.rows * a.nf * a.nb + X::G - 1) / X::G;
-  k_x_c2r<T, N / 2, LC::TQ, X::G, typename LC::RL><<<dim3((unsigned)grid), dim3(X::G * LC::TQ), 0, s>>>(a);
-  return hipGetLastError();
-}
-
-template <typename T, int N>
-hipError_t x_r2c_n(XArgs<T> a, hipStream_t s) {
-  using LC = LenCfg<N / 2>;
-  using X = XCfg<T, N / 2, LC::TQ>;
-  const long grid = (a.rows * a.nf * a.nb + X::G - 1) / X::G;
-  k_x_r2c<T, N / 2, LC::TQ, X::G, typename LC::RL><<<dim3((unsigned)grid), dim3(X::G * LC::TQ), 0, s>>>(a);
-  return hipGetLastError();
-}
-
 // packed form: full-length complex transforms, two real rows each
 template <typename T, int N, int I>
 hipError_t x_prod_pk_v(bool mhd, bool els, XArgs<T> a, hipStream_t s) {
@@ -366,30 +348,6 @@ bool mhd_supported(int N) {
 #undef PS_CASE
   }
   return false;
-}
-
-template <typename T>
-hipError_t launch_x_c2r(int N, XArgs<T> a, hipStream_t s) {
-  switch (N) {
-#define PS_CASE(NN) \
-  case NN:          \
-    return x_c2r_n<T, NN>(a, s);
-    PS_FOR_EACH_N(PS_CASE)
-#undef PS_CASE
-  }
-  return hipErrorInvalidValue;
-}
-
-template <typename T>
-hipError_t launch_x_r2c(int N, XArgs<T> a, hipStream_t s) {
-  switch (N) {
-#define PS_CASE(NN) \
-  case NN:          \
-    return x_r2c_n<T, NN>(a, s);
-    PS_FOR_EACH_N(PS_CASE)
-#undef PS_CASE
-  }
-  return hipErrorInvalidValue;
 }
 
 template <typename T>

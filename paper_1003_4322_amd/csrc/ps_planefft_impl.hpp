@@ -1,0 +1,72 @@
+// ps_planefft_impl.hpp -- launchers of the plain real transforms along x and of
+// whole planes, included by one translation unit per dtype
+// (k_planefft_<dtype>.hip).
+#pragma once
+
+#include "ps_launch.hpp"
+#include "ps_planefft.hpp"
+#include "ps_xfft.hpp"
+
+namespace ps {
+
+template <class F>
+bool planefft_pick(int N, F&& f) {
+  switch (N) {
+#define PS_CASE(NN)                            \
+  case NN:                                     \
+    f(std::integral_constant<int, NN>{});      \
+    return true;
+    PS_FOR_EACH_PLANEFFT_N(PS_CASE)
+#undef PS_CASE
+  }
+  return false;
+}
+
+template <typename T>
+bool planefft_fits(int nx, int ny) {
+  bool fits = false;
+  if (nx == ny) planefft_pick(nx, [&](auto n) { fits = PlaneFftCfg<T, decltype(n)::value>::FITS; });
+  return fits;
+}
+
+template <typename T>
+hipError_t launch_planefft(int N, int dir, PlaneFftArgs<T> a, hipStream_t s) {
+  hipError_t r = hipErrorInvalidValue;
+  const long grid = (long)a.nz * a.nf * a.nb;
+  if (grid <= 0) return hipSuccess;
+  planefft_pick(N, [&](auto n) {
+    using P = PlaneFftCfg<T, decltype(n)::value>;
+    if constexpr (P::FITS) {
+      if (dir == INV)
+        k_plane_c2r<T, decltype(n)::value><<<dim3((unsigned)grid), dim3(P::NT), 0, s>>>(a);
+      else
+        k_plane_r2c<T, decltype(n)::value><<<dim3((unsigned)grid), dim3(P::NT), 0, s>>>(a);
+      r = hipGetLastError();
+    }
+  });
+  return r;
+}
+
+template <typename T>
+hipError_t launch_xfft(int N, int dir, XFftArgs<T> a, hipStream_t s) {
+  const unsigned long total = (unsigned long)a.pairs * a.nf * a.nb;
+  if (total == 0) return hipSuccess;
+  if (total >= 0xffffffffUL) return hipErrorInvalidValue;  // the kernels number row pairs in 32 bits
+  switch (N) {
+#define PS_CASE(NN)                                                        \
+  case NN: {                                                               \
+    using X = XFftCfg<T, NN>;                                              \
+    const dim3 grid((unsigned)((total + X::G - 1) / X::G)), block(X::NT);  \
+    if (dir == INV)                                                        \
+      k_x_c2r<T, NN><<<grid, block, 0, s>>>(a);                            \
+    else                                                                   \
+      k_x_r2c<T, NN><<<grid, block, 0, s>>>(a);                            \
+    return hipGetLastError();                                              \
+  }
+    PS_FOR_EACH_N(PS_CASE)
+#undef PS_CASE
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace ps
