@@ -598,7 +598,7 @@ ps_status upload_disk_tiles(ps_plan p, const Class& c) {
   if (p->dtiles.count(key)) return PS_OK;
   ps::DiskTiles& dt = p->dtiles[key];
   unsigned widths = ps::z_curl_widths<T>(c.nz) | ps::z_epi_widths<T>(c.nz);
-  if (c.nz <= 128) widths |= 1u << 8 | 1u << 16;  // the field-parallel passes
+  widths |= 1u << 8 | 1u << 16;  // the field-parallel passes
   // all lists in one allocation and one copy
   std::vector<int> all;
   std::map<int, size_t> first;

@@ -153,6 +153,7 @@ struct ZV {
   bool direct;  // z_curl: gather inputs per output field instead of holding them in registers
   bool wide = false;  // wide schedule (LenWide: a last radix of 4 over twice the threads)
   bool tws = false;   // strided passes: twiddles staged in LDS beside the tile
+  bool tile = false;  // z_epi: fields combined and in LDS side by side, in two groups (k_z_epi_tile)
 };
 struct XV {
   int rb_ns, rb_mhd;  // rows per workgroup (reduced while the LDS tile would not fit)
@@ -170,7 +171,8 @@ constexpr ZV ZCURL_V[] = {{1, 1, 1, false, false}, {1, 2, 1, false, false}, {1, 
 constexpr ZV ZEPI_V[] = {{0, 1, 1, false}, {1, 1, 1, false}, {1, 1, 2, false}, {1, 1, 1, true},
                          {2, 1, 1, false}, {1, 2, 1, false}, {1, 2, 2, false}, {2, 2, 1, false},
                          {0, 1, 1, false, false, true}, {1, 1, 1, false, false, true},
-                         {1, 1, 2, false, false, true}, {2, 1, 1, false, false, true}};
+                         {1, 1, 2, false, false, true}, {2, 1, 1, false, false, true},
+                         {0, 1, 1, true, false, false, false, true}};
 constexpr ZV STR_V[] = {{0, 1, 1, false}, {1, 1, 1, false}, {0, 1, 1, true}, {1, 1, 1, true},
                         {0, 1, 1, true, false, false, true}, {0, 1, 1, false, false, false, true}};
 constexpr XV XPROD_V[] = {{2, 1, 0, false}, {4, 2, 0, false}, {4, 2, 1, false}, {2, 1, 1, false},
@@ -250,17 +252,32 @@ constexpr int pick_zcurl(bool f32, int n, bool mhd, bool els, bool prune) {
 // (MHD 512: Elsasser FP32 1123 -> 1036, FP64 2296 -> 1950; rotational FP64 7561 ->
 // 7009); half-width tiles at 192 in FP32 (NS pr 41 -> 29) and for the NS
 // divergence form at 256 and 512; z+ and z- in two workgroups for Elsasser
-// fields below 256 and FP64 at 384 (192 FP64 166 -> 154); half-width tiles for
+// fields at 192 in FP32 (71 -> 65); half-width tiles for
 // rotational MHD at 768 and 1024 (MHD 64 x 96 x 768 FP32, a step: 1262 against
 // 1384 with the wide schedule).
+// The fields of a tile side by side (12) for MHD at 384 and, Elsasser, 512
+// (k_z_epi_tile's comment has both sides).
 constexpr int pick_zepi(bool f32, int n, bool mhd, bool els) {
   if (n < 256) {
-    if (mhd && els) return n >= 96 ? 5 : 0;
+    if (mhd && els) return n == 192 ? 5 : 0;
     return f32 && n == 192 ? 1 : !f32 && mhd && n == 96 ? 1 : 0;
   }
-  if (mhd && els) return n == 256 ? (f32 ? 9 : 8) : n == 384 ? (f32 ? 8 : 5) : f32 ? 8 : 9;
-  if (mhd) return n == 384 ? 0 : n >= 768 ? 5 : n == 512 && !f32 ? 9 : 8;
+  if (mhd && els) return n == 256 ? (f32 ? 9 : 8) : n <= 512 ? 12 : f32 ? 8 : 9;
+  if (mhd) return n == 384 ? (f32 ? 12 : 0) : n >= 768 ? 5 : n == 512 && !f32 ? 9 : 8;
   return f32 && els && (n == 256 || n == 512) ? 9 : 0;
+}
+
+// Lengths below 256: k_z_epi_tile's groups (0: k_z_epi instead) and columns per
+// tile, for the divergence forms where the columns are too many for
+// k_z_epi_field (16 columns of 96 or 128 FP32 points in two groups still leave
+// two workgroups per CU: 8 boxes of MHD 96^3 47 us against 52 with 8 columns).
+struct EpiTilePick {
+  int groups, tx;
+};
+constexpr EpiTilePick pick_epi_tile(bool f32, int n, bool mhd, bool els) {
+  if (!els || n < 96 || n > 192 || (n == 192 && (!mhd || f32))) return {0, 0};
+  if (n == 96 && !mhd) return {1, 8};
+  return {2, f32 ? 16 : 8};
 }
 
 }  // namespace ps

@@ -82,6 +82,8 @@ inline bool z_curl_by_field(int nz, long columns) { return nz <= ZCURL_FIELD_MAX
 // boxes of 64^3 646 to 611) and up to 128 points while the columns are few
 // (NS 96^3 122 to 104, 1608 columns; NS 96^3 FP64, 4704 columns, 198 to 213; NS
 // 128^3 145 to 135, 2900 columns; unpruned, 8320 columns, 196 to 221).
+// (48 boxes of NS 64^3: k_z_epi_tile ties with it, 365 us a step; 200 of 32^3:
+// 201 against 194.)
 inline bool z_epi_by_field(int nz, long columns) { return nz <= 64 || (nz <= 128 && columns <= 4096); }
 template <typename T>
 hipError_t launch_z_curl_field(int N, bool mhd, bool els, ZCurlArgs<T> a, const DiskTiles* dt, hipStream_t s);

@@ -8,6 +8,7 @@
 
 #include "ps_config.hpp"
 #include "ps_launch.hpp"
+#include "ps_zfield.hpp"
 
 namespace ps {
 
@@ -148,18 +149,40 @@ unsigned z_curl_widths(int N) {
 }
 
 // ---------------- forward z pass + epilogue ----------------
+template <typename T, int N, int TX, class LC, bool MHD, bool ELS, int PH>
+hipError_t z_epi_tile(ZEpiArgs<T> a, const DiskTiles* dt, hipStream_t s) {
+  if (a.g.nz != N) return hipErrorInvalidValue;
+  a.ntile = cdiv(a.g.nx / 2 + 1, TX);
+  const long grid = z_grid<TX>(a.g.ny, a.ntile, a.nb, a.prune && a.mode != 0, dt, a.tiles, a.ntl);
+  k_z_epi_tile<T, N, LC::TQ, TX, typename LC::RL, MHD, ELS, PH>
+      <<<dim3((unsigned)grid), dim3(EpiTileCfg<T, N, LC::TQ, TX, MHD, ELS, PH>::NT), 0, s>>>(a);
+  return hipGetLastError();
+}
+
 template <typename T, int N, int I, bool MHD, bool ELS = false>
 hipError_t z_epi_v(ZEpiArgs<T> a, const DiskTiles* dt, hipStream_t s) {
   constexpr ZV v = ZEPI_V[I];
-  using LC = ZepiSched<N, I>;
-  constexpr int TX = StridedTX<T, N, LC::TQ, v.sh>::value;
-  constexpr int SPLIT = ELS && MHD && v.split >= 2 ? 2 : 1;
-  if (a.g.nz != N) return hipErrorInvalidValue;
-  a.ntile = cdiv(a.g.nx / 2 + 1, TX);
-  const long grid = z_grid<TX>(a.g.ny, a.ntile, a.nb, a.prune && a.mode != 0, dt, a.tiles, a.ntl) * SPLIT;
-  k_z_epi<T, N, LC::TQ, TX, typename LC::RL, MHD, waves_per_simd(v.minb, TX * LC::TQ), ELS, SPLIT>
-      <<<dim3((unsigned)grid), dim3(TX * LC::TQ), 0, s>>>(a);
-  return hipGetLastError();
+  if constexpr (v.tile) {
+    // 8 columns, or 4 where 8 do not fit; variant 0 where neither does
+    using A = LenAlt<N>;
+    constexpr int PH = MHD || ELS ? 2 : 1;  // NS rotational has one group of fields
+    if constexpr (EpiTileCfg<T, N, A::TQ, 8, MHD, ELS, PH>::FITS)
+      return z_epi_tile<T, N, 8, A, MHD, ELS, PH>(a, dt, s);
+    else if constexpr (EpiTileCfg<T, N, A::TQ, 4, MHD, ELS, PH>::FITS)
+      return z_epi_tile<T, N, 4, A, MHD, ELS, PH>(a, dt, s);
+    else
+      return z_epi_v<T, N, 0, MHD, ELS>(a, dt, s);
+  } else {
+    using LC = ZepiSched<N, I>;
+    constexpr int TX = StridedTX<T, N, LC::TQ, v.sh>::value;
+    constexpr int SPLIT = ELS && MHD && v.split >= 2 ? 2 : 1;
+    if (a.g.nz != N) return hipErrorInvalidValue;
+    a.ntile = cdiv(a.g.nx / 2 + 1, TX);
+    const long grid = z_grid<TX>(a.g.ny, a.ntile, a.nb, a.prune && a.mode != 0, dt, a.tiles, a.ntl) * SPLIT;
+    k_z_epi<T, N, LC::TQ, TX, typename LC::RL, MHD, waves_per_simd(v.minb, TX * LC::TQ), ELS, SPLIT>
+        <<<dim3((unsigned)grid), dim3(TX * LC::TQ), 0, s>>>(a);
+    return hipGetLastError();
+  }
 }
 
 template <typename T, int N, int I>
@@ -168,18 +191,24 @@ hipError_t z_epi_m(bool mhd, bool els, ZEpiArgs<T> a, const DiskTiles* dt, hipSt
   return mhd ? z_epi_v<T, N, I, true>(a, dt, s) : z_epi_v<T, N, I, false>(a, dt, s);
 }
 
+// lengths without variants: the default
+template <typename T, int N, bool MHD, bool ELS>
+hipError_t z_epi_d(ZEpiArgs<T> a, const DiskTiles* dt, hipStream_t s) {
+  constexpr EpiTilePick t = pick_epi_tile(sizeof(T) == 4, N, MHD, ELS);
+  if constexpr (t.groups != 0)
+    return z_epi_tile<T, N, t.tx, LenCfg<N>, MHD, ELS, t.groups>(a, dt, s);
+  else
+    return z_epi_v<T, N, pick_zepi(sizeof(T) == 4, N, MHD, ELS), MHD, ELS>(a, dt, s);
+}
+
 template <typename T, int N>
 hipError_t z_epi_n(bool mhd, bool els, int var, ZEpiArgs<T> a, const DiskTiles* dt, hipStream_t s) {
   if constexpr (has_variants(N)) {
     return pick(var, std::make_integer_sequence<int, NZEPI>{},
                 [&](auto I) { return z_epi_m<T, N, decltype(I)::value>(mhd, els, a, dt, s); });
   } else {
-    constexpr bool F = sizeof(T) == 4;
-    if (els)
-      return mhd ? z_epi_v<T, N, pick_zepi(F, N, true, true), true, true>(a, dt, s)
-                 : z_epi_v<T, N, pick_zepi(F, N, false, true), false, true>(a, dt, s);
-    return mhd ? z_epi_v<T, N, pick_zepi(F, N, true, false), true>(a, dt, s)
-               : z_epi_v<T, N, pick_zepi(F, N, false, false), false>(a, dt, s);
+    if (els) return mhd ? z_epi_d<T, N, true, true>(a, dt, s) : z_epi_d<T, N, false, true>(a, dt, s);
+    return mhd ? z_epi_d<T, N, true, false>(a, dt, s) : z_epi_d<T, N, false, false>(a, dt, s);
   }
 }
 
@@ -198,7 +227,9 @@ hipError_t launch_z_epi(int N, bool mhd, bool els, int var, ZEpiArgs<T> a, const
 
 template <typename T, int N, int... I>
 constexpr unsigned zepi_ws(std::integer_sequence<int, I...>) {
-  return (0u | ... | (1u << StridedTX<T, N, ZepiSched<N, I>::TQ, ZEPI_V[I].sh>::value));
+  // (k_z_epi_tile's 4, 8 or 16 columns too)
+  return ((1u << 8 | (has_variants(N) ? 1u << 4 : 1u << 16)) | ... |
+          (1u << StridedTX<T, N, ZepiSched<N, I>::TQ, ZEPI_V[I].sh>::value));
 }
 template <typename T>
 unsigned z_epi_widths(int N) {

@@ -1,6 +1,5 @@
-// ps_zfield.hpp -- z passes that transform all fields of a column tile side by
-// side instead of one after another, for boxes too small to fill the chip with
-// column tiles alone.
+// ps_zfield.hpp -- z passes that transform the fields of a column tile side by
+// side instead of one after another.
 #pragma once
 
 #include "ps_config.hpp"
@@ -258,6 +257,316 @@ __global__ __launch_bounds__(NG* TX* TQ) void k_z_epi_field(ZEpiArgs<T> a) {
       vis = vis + cor[f % 3];
       const C2<T> old = a.mode == 1 ? zz[i][f] : z0[i][f];
       dst[f * a.out_fs + pos] = old + a.h * (nh[f] - vis);
+    }
+  }
+}
+
+// Forward z pass + epilogue (k_z_epi's outputs and modes) with the fields of a
+// column tile combined before the transform and in LDS side by side.
+//
+// A column's (kx, ky) is fixed, so with k = (kx, ky, kz), kp = |(kx, ky)| and the
+// horizontal unit vectors eL = (kx, ky) / kp = (cx, cy) and eT = (-cy, cx) (eL =
+// (1, 0) where kp = 0), linear combinations over the horizontal indices may be
+// taken before the transform along z.  The projection keeps a vector's eT
+// component and, of its (eL, ez) part, the component across k:
+//   P(k) a = aT eT + s (-kz eL + kp ez),  s = (kp az - kz aL) / k^2.
+// For the divergence forms, a_i = sum_j k_j T_ij, this needs from T = z+ z- (and
+// its transpose for z-) only
+//   T0+ = eT T eL, T0- = eL T eT, Q = eL T eL, T1+ = eT T ez, B = eL T ez,
+//   T1- = ez T eT, A = ez T eL   (T less its isotropic part, T_zz = 0):
+//   aT+- = kp T0+- + kz T1+-, aL+ = kp Q + kz B, az+ = kp A, aL- = kp Q + kz A,
+//   az- = kp B:
+// seven transforms instead of eight (MHD), and for the symmetric u u (T1+ = T1-,
+// A = B, T0+ = T0-) four instead of five (NS).  The rotational forms transform
+// their three or six fields as they are.
+//
+// Tiles: PH = 1 keeps all of them in LDS at once; PH = 2 does the two groups
+// {T0, Q} and {T1, A, B} (MHD rotational: u x w + j x b, then u x b) one after
+// the other, half the LDS.  Every thread first loads its elements of the
+// group's input fields and writes their combinations to the tiles (the second
+// group's and the state's loads are in flight during the first transforms);
+// TX x TQ threads then transform each tile, all tiles at once; and each thread
+// finishes the modes (c, kz) of its elements from LDS.
+//
+// Bound by memory (64-byte pieces of rows a plane apart) and the exchanges.
+// One barrier-separated transform of a whole group, a seventh or a fifth fewer
+// transforms and no accumulators held across them, against k_z_epi, launch
+// times, us: MHD Elsasser 384^3 FP32 522 -> 384, FP64 1099 -> 757, 512^3 FP32 971
+// -> 900, FP64 1820 -> 1650, 192^3 FP64 136 -> 82, 8 boxes of 96^3 FP32 73 -> 47;
+// NS divergence form, 48 boxes of 64^3 FP32 61 -> 40, 16 of 96^3 53 -> 37, 4 of
+// 128^3 33 -> 29.  It loses where k_z_epi's registers suffice (NS 256^3 FP32 55
+// -> 70, MHD 256^3 FP32 123 -> 134) and, by its extra pass through LDS, to
+// k_z_epi_field where a launch is one round of latency (NS 64^3 5.6 -> 6.3).
+template <bool MHD, bool ELS>
+struct EpiGroups {
+  static constexpr int in0 = ELS ? (MHD ? 4 : 3) : 3, in1 = ELS ? (MHD ? 4 : 2) : MHD ? 3 : 0;
+  static constexpr int out0 = ELS ? (MHD ? 3 : 2) : 3, out1 = ELS ? (MHD ? 4 : 2) : MHD ? 3 : 0;
+  // input field i of group g
+  static constexpr int field(int g, int i) {
+    if (ELS && MHD) return g == 0 ? (i < 2 ? i : i + 1) : (i == 0 ? 2 : 4 + i);  // 00 01 10 11; 02 12 20 21
+    return g == 0 ? i : in0 + i;                                               // NS: 00 11 01; 02 12
+  }
+  static constexpr int nin(int g) { return g == 0 ? in0 : in1; }
+  static constexpr int nout(int g) { return g == 0 ? out0 : out1; }
+  // tiles that are in LDS together
+  static constexpr int tiles(int ph) { return ph == 1 ? out0 + out1 : out0 > out1 ? out0 : out1; }
+  // tile t of group g from the group's inputs
+  template <typename T>
+  __device__ __forceinline__ static C2<T> tile(int g, int t, const C2<T>* x, T cx, T cy) {
+    if constexpr (!ELS) {
+      return x[t];
+    } else if (g == 0) {
+      if constexpr (MHD) {
+        const C2<T> d = (cx * cy) * (x[3] - x[0]);
+        if (t == 0) return (cx * cx) * x[2] + d - (cy * cy) * x[1];  // T0+
+        if (t == 1) return (cx * cx) * x[1] + d - (cy * cy) * x[2];  // T0-
+        return (cx * cx) * x[0] + (cx * cy) * (x[1] + x[2]) + (cy * cy) * x[3];
+      } else {
+        if (t == 0) return (cx * cx - cy * cy) * x[2] + (cx * cy) * (x[1] - x[0]);
+        return (cx * cx) * x[0] + (T(2) * cx * cy) * x[2] + (cy * cy) * x[1];
+      }
+    } else {
+      if (t == 0) return cx * x[1] - cy * x[0];  // T1+
+      if (t == 1) return cx * x[0] + cy * x[1];  // B
+      if constexpr (MHD) {
+        if (t == 2) return cx * x[3] - cy * x[2];  // T1-
+        return cx * x[2] + cy * x[3];              // A
+      }
+      return zero2<T>();
+    }
+  }
+};
+
+template <typename T, int L, int TQ, int TX, bool MHD, bool ELS, int PH>
+struct EpiTileCfg {
+  using G = EpiGroups<MHD, ELS>;
+  static constexpr int TILES = G::tiles(PH), ROWS = pad8(L - 1) + 1;
+  // thread groups: one per tile, fewer where 1024 threads do not hold them
+  static constexpr int NG = [] {
+    const int most = 1024 / (TX * TQ) < 1 ? 1 : 1024 / (TX * TQ);
+    return cdiv(TILES, cdiv(TILES, most));
+  }();
+  static constexpr int NT = NG * TX * TQ;
+  static constexpr int LDS = (TILES * ROWS * TX + L) * (int)sizeof(C2<T>);
+  static constexpr bool FITS = LDS <= 163840 && NT <= 1024;
+};
+
+template <typename T, int L, int TQ, int TX, class RL, bool MHD, bool ELS, int PH>
+__global__ __launch_bounds__((EpiTileCfg<T, L, TQ, TX, MHD, ELS, PH>::NT)) void k_z_epi_tile(ZEpiArgs<T> a) {
+  using E = Stockham<T, L, TQ, FWD, RL>;
+  using Cfg = EpiTileCfg<T, L, TQ, TX, MHD, ELS, PH>;
+  using G = EpiGroups<MHD, ELS>;
+  constexpr int NF = MHD ? 6 : 3;  // state fields
+  constexpr int NG = Cfg::NG, NT = Cfg::NT, NO = E::LAST_NB * E::RL_;
+  constexpr int PTS = cdiv(L * TX, NT);
+  constexpr bool EXACT = (L * TX) % NT == 0;
+  using Lay = LayColPad8;
+  constexpr int TILE = Cfg::ROWS * TX;
+  // the second group's and the state's loads go out before a transform, unless
+  // its registers leave no room for them (16 values a thread, the first group's
+  // results and the state of a long column: 971 us at 512 FP32 with spills,
+  // 1045 without this line; 384 FP32 405 without the early loads, 384 with)
+  constexpr bool AHEAD = L < 512;
+  __shared__ C2<T> smem[Cfg::TILES * TILE + L];
+  C2<T>* const tws = smem + Cfg::TILES * TILE;
+  const int tid = threadIdx.x, c = tid % TX, q = tid / TX % TQ, grp = tid / (TX * TQ);
+  const Grid& g = a.g;
+  const int blk = gridDim.x >= ZREMAP ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+  const ZTile zt = z_tile(blk, a.ntile, g.ny, a.tiles, a.ntl);
+  const int col = zt.tile * TX + c, ky = zt.ky, kyw = wav(ky, g.ny);
+  if (a.prune && a.mode != 0 && !g.disk(zt.tile * TX, kyw)) return;
+  const bool ok = col < g.nx / 2 + 1;
+  const bool disk = ok && (!a.prune || g.disk(col, kyw));
+  const long in_es = (long)g.ny * a.in_pitch, out_es = (long)g.ny * a.out_pitch;
+  const C2<T>* in = a.in + zt.box * a.in_bs + ky * a.in_pitch + col;
+  // element i of this thread: column c, row (grid plane, then kz) zi(i)
+  auto zi = [&](int i) { return tid / TX + i * (NT / TX); };
+  auto inside = [&](int i) { return EXACT || zi(i) < L; };
+  const T kx = a.sx * (T)col, ky_ = a.sy * (T)kyw;
+  const T kp2 = kx * kx + ky_ * ky_, kp = sqrt(kp2);
+  const T ikp = kp2 > T(0) ? T(1) / kp : T(0);
+  const T cx = kp2 > T(0) ? kx * ikp : T(1), cy = ky_ * ikp;
+  TwFill<T, L, NT, RL> fill;
+  fill.load(a.tw, tid);
+  auto load0 = [&](C2<T>(&x)[PTS][G::in0]) {
+#pragma unroll
+    for (int i = 0; i < PTS; ++i)
+#pragma unroll
+      for (int f = 0; f < G::in0; ++f)
+        x[i][f] = disk && inside(i) ? in[G::field(0, f) * a.in_fs + zi(i) * in_es] : zero2<T>();
+  };
+  constexpr int IN1 = G::in1 > 0 ? G::in1 : 1;
+  auto load1 = [&](C2<T>(&x)[PTS][IN1]) {
+#pragma unroll
+    for (int i = 0; i < PTS; ++i)
+#pragma unroll
+      for (int f = 0; f < G::in1; ++f)
+        x[i][f] = disk && inside(i) ? in[G::field(1, f) * a.in_fs + zi(i) * in_es] : zero2<T>();
+  };
+  // tiles [t0, t0 + nout) of LDS from a group's inputs
+  auto put = [&](auto gc, int t0, const auto& x) {
+    constexpr int gi = decltype(gc)::value;
+#pragma unroll
+    for (int i = 0; i < PTS; ++i)
+      if (inside(i)) {
+#pragma unroll
+        for (int t = 0; t < G::nout(gi); ++t)
+          smem[(t0 + t) * TILE + c + Lay::off(zi(i), TX)] = G::template tile<T>(gi, t, x[i], cx, cy);
+      }
+  };
+  // transform the first n tiles in place (every thread takes part in the barriers)
+  auto transform = [&](auto nc) {
+    constexpr int n = decltype(nc)::value, NR = cdiv(n, NG);
+    C2<T> v[NR][E::SLOTS];
+    __syncthreads();  // the tiles (and the staged twiddles) are written
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int t = grp + r * NG;
+      C2<T>* tile = smem + (t < n ? t : 0) * TILE + c;
+      E::template run_tw<Lay>(v[r], tile, TX, q, TwStaged<T>{tws},
+                              [&](int, int idx) { return tile[Lay::off(idx, TX)]; }, t < n);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int t = grp + r * NG;
+      if (t < n) {
+#pragma unroll
+        for (int s = 0; s < NO; ++s)
+          if (E::last_valid(q, s)) smem[t * TILE + c + Lay::off(E::last_index(q, s), TX)] = v[r][s];
+      }
+    }
+    __syncthreads();
+  };
+  const int kperp2 = g.perp(col, kyw);
+  const long base = zt.box * a.out_bs + ky * a.out_pitch + col;
+  auto touched = [&](int i) {  // element i is a mode the call writes
+    return ok && inside(i) && (a.mode == 0 || !a.prune || g.keep_p(kperp2, wav(zi(i), L)));
+  };
+  // the state: zz the fields the viscous term acts on
+  C2<T> zz[PTS][NF];
+  auto load_state = [&] {
+    if (a.mode == 0) return;
+    const C2<T>* zv = a.mode == 1 ? a.st0 : a.st1;
+#pragma unroll
+    for (int i = 0; i < PTS; ++i) {
+      const bool t = touched(i);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) zz[i][f] = t ? zv[f * a.out_fs + base + zi(i) * out_es] : zero2<T>();
+    }
+  };
+  C2<T> h0[PTS][G::out0];  // the first group's results (PH = 2)
+  using g0_ = std::integral_constant<int, 0>;
+  using g1_ = std::integral_constant<int, 1>;
+  {
+    C2<T> x0[PTS][G::in0], x1[PTS][IN1];
+    load0(x0);
+    if constexpr (PH == 1) {
+      load1(x1);
+      load_state();
+      fill.store(tws, tid);
+      put(g0_{}, 0, x0);
+      if constexpr (G::in1 > 0) put(g1_{}, G::out0, x1);
+      transform(std::integral_constant<int, Cfg::TILES>{});
+    } else {
+      fill.store(tws, tid);
+      put(g0_{}, 0, x0);
+      if constexpr (AHEAD) load1(x1);
+      transform(std::integral_constant<int, G::out0>{});
+#pragma unroll
+      for (int i = 0; i < PTS; ++i)
+#pragma unroll
+        for (int t = 0; t < G::out0; ++t)
+          h0[i][t] = inside(i) ? smem[t * TILE + c + Lay::off(zi(i), TX)] : zero2<T>();
+      __syncthreads();
+      if constexpr (!AHEAD) load1(x1);
+      put(g1_{}, 0, x1);
+      if constexpr (AHEAD) load_state();
+      transform(std::integral_constant<int, G::out1>{});
+      if constexpr (!AHEAD) load_state();
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < PTS; ++i) {
+    if (!touched(i)) continue;
+    const int kzi = zi(i), ikz = wav(kzi, L);
+    const bool zero_mode = col == 0 && kyw == 0 && ikz == 0;
+    const bool keep = !zero_mode && g.keep_p(kperp2, ikz);
+    const T kz = a.sz * (T)ikz, k2 = kp2 + kz * kz;
+    auto lds = [&](int t) -> C2<T> { return smem[t * TILE + c + Lay::off(kzi, TX)]; };
+    auto at0 = [&](int t) -> C2<T> { return a.scale * (PH == 1 ? lds(t) : h0[i][t]); };
+    auto at1 = [&](int t) -> C2<T> { return a.scale * lds(PH == 1 ? G::out0 + t : t); };
+    const long pos = base + kzi * out_es;
+    C2<T> z0[NF];
+    if (a.mode == 2) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) z0[f] = a.st0[f * a.out_fs + pos];
+    }
+    C2<T> nh[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) nh[f] = zero2<T>();
+    if (keep) {
+      const T ik2 = T(1) / k2;
+      if constexpr (ELS) {
+        // -i P(k) a from its eT component and s
+        auto put3 = [&](C2<T>* n, C2<T> aT, C2<T> s) {
+          const C2<T> h = kz * s;
+          n[0] = mul_mi(zero2<T>() - (cy * aT + cx * h));
+          n[1] = mul_mi(cx * aT - cy * h);
+          n[2] = mul_mi(kp * s);
+        };
+        if constexpr (MHD) {
+          const C2<T> Q = kp * at0(2), t1p = at1(0), B = at1(1), t1m = at1(2), A = at1(3);
+          put3(nh, kp * at0(0) + kz * t1p, ik2 * (kp2 * A - kz * (Q + kz * B)));
+          put3(nh + 3, kp * at0(1) + kz * t1m, ik2 * (kp2 * B - kz * (Q + kz * A)));
+        } else {
+          const C2<T> B = at1(1);
+          put3(nh, kp * at0(0) + kz * at1(0), ik2 * (kp2 * B - kz * (kp * at0(1) + kz * B)));
+        }
+      } else {
+        C2<T> n0 = at0(0), n1 = at0(1), n2 = at0(2);
+        const C2<T> kn = kx * n0 + ky_ * n1 + kz * n2;
+        nh[0] = n0 - (kx * ik2) * kn;
+        nh[1] = n1 - (ky_ * ik2) * kn;
+        nh[2] = n2 - (kz * ik2) * kn;
+        if constexpr (MHD) {
+          // kept modes have no Nyquist index: derivatives use k itself
+          const C2<T> e0 = at1(0), e1 = at1(1), e2 = at1(2);
+          const C2<T> c0 = mul_i(ky_ * e2 - kz * e1), c1 = mul_i(kz * e0 - kx * e2), c2 = mul_i(kx * e1 - ky_ * e0);
+          nh[3] = nh[0] - c0;
+          nh[4] = nh[1] - c1;
+          nh[5] = nh[2] - c2;
+          nh[0] = nh[0] + c0;
+          nh[1] = nh[1] + c1;
+          nh[2] = nh[2] + c2;
+        }
+      }
+    }
+    if (a.mode == 0) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) a.out[f * a.out_fs + pos] = nh[f];
+      continue;
+    }
+    C2<T>* dst = a.mode == 1 ? a.out : const_cast<C2<T>*>(a.st0);
+    C2<T> cor[3] = {zero2<T>(), zero2<T>(), zero2<T>()};
+    if (a.rot && !zero_mode) {
+      C2<T> u[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) u[d] = MHD ? T(0.5) * (zz[i][d] + zz[i][(d + 3) % NF]) : zz[i][d];
+      const C2<T> w0 = a.w2y * u[2] - a.w2z * u[1];
+      const C2<T> w1 = a.w2z * u[0] - a.w2x * u[2];
+      const C2<T> w2 = a.w2x * u[1] - a.w2y * u[0];
+      const C2<T> kw = (T(1) / k2) * (kx * w0 + ky_ * w1 + kz * w2);
+      cor[0] = w0 - kx * kw;
+      cor[1] = w1 - ky_ * kw;
+      cor[2] = w2 - kz * kw;
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      C2<T> vis = (a.nua * k2) * zz[i][f];
+      if constexpr (MHD) vis = vis + (a.nub * k2) * zz[i][(f + 3) % NF];
+      vis = vis + cor[f % 3];
+      dst[f * a.out_fs + pos] = (a.mode == 1 ? zz[i][f] : z0[f]) + a.h * (nh[f] - vis);
     }
   }
 }
