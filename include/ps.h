@@ -220,7 +220,12 @@ ps_status ps_mhd_spectrum(ps_plan p, const void *zhat, double *spec_dev, double 
 
 /* Kernel variants.  Pass kinds: "y", "z" (plain strided passes), "z_curl",
  * "z_epi", "x_prod"; the tile width, radix schedule or register/LDS trade-off
- * of a pass (results are identical up to rounding order).  Kind "batch":
+ * of a pass (results are identical up to rounding order).  A pass kind that
+ * was neither set nor tuned takes a default chosen by length, element type,
+ * form and pruning; setting "form" or "prune" chooses it anew.  Small boxes
+ * run kernels without variants (z passes that transform the fields side by
+ * side, whole planes kept in LDS): there a variant changes nothing.
+ * Kind "batch":
  * 0 = one launch per pass for each run of consecutive equal-size boxes
  * (default), 1 = one launch per box (baseline).  Kind "prune": 1 = the
  * step and the nonlinear terms skip everything the 2/3 rule makes zero (pencils
@@ -251,9 +256,11 @@ ps_status ps_mhd_spectrum(ps_plan p, const void *zhat, double *spec_dev, double 
  * last-level cache; for v = 7..9, 2^(v-3) slabs (16, 32, 64) as two chains,
  * even and odd slabs, on two helper streams, so that the two slabs in flight
  * still fit the last-level cache while each fills the other's launch gaps;
- * 0 = one slab on the plan's stream (default; ps_plan_autotune chooses among
- * 0 and 4..6, the settings whose launches do not overlap, unless "overlap"
- * is 1).  Every setting computes the same step bit for bit.  Kind "overlap"
+ * 0 = one slab on the plan's stream (ps_plan_autotune chooses among 0 and
+ * 4..6, the settings whose launches do not overlap, unless "overlap" is 1).
+ * A plan whose "pipe" was neither set nor tuned (it reads as 0) runs one slab,
+ * or, unpruned with fields of more than twice the last-level cache, in-order
+ * slabs that fit it.  Every setting computes the same step bit for bit.  Kind "overlap"
  * (0 default, 1): whether ps_plan_autotune may also choose the two-chain
  * settings 7..9, for a caller who wants the fastest step over per-kernel
  * timings (a launch's duration is no longer its own when two overlap); it

@@ -458,11 +458,28 @@ struct Seq {
     return st;
   }
 
+  // In-order slabs of the y / x / y passes where nobody has set or tuned "pipe":
+  // as many as leave a slab's widest field set 230 MB, so that its chain finds
+  // its data in the 256 MB last-level cache.  The three passes alone, us at 1
+  // slab / the count chosen / twice that: NS 512^3 FP32 3358 / 2992 / 3078, MHD
+  // 256^3 FP32 878 / 784 / 811, NS 256^3 FP64 908 / 771 / 826; whole steps MHD 256^3
+  // FP32 3549 -> 3353, 48 boxes of MHD 64^3 FP32 3202 -> 2921, NS 1024^3 FP32 107.8
+  // -> 107.0 ms.  Two slabs lose more in launches than they gain (NS 256^3 FP32
+  // 355 / 376, NS 192^3 FP64 289 / 303), and so do pruned boxes of 384^3 (NS FP64
+  // 2204 / 2302): those keep one slab until they are tuned, as do planes that
+  // one kernel takes through all three passes.
+  int default_slabs(bool mhd) const {
+    if (p->prune || ps::plane_fits<T>(b.nx, b.ny, mhd, els(mhd), p->prune)) return 1;
+    const double fields = (double)std::max(nphys(mhd), nprod(mhd)) * nb * b.ncp * cs();
+    const int slabs = (int)std::ceil(fields / 230e6);
+    return slabs < 3 ? 1 : slabs;
+  }
+
   ps_status rhs(const C* src, bool mhd, int mode, C* out, const C* st0, const C* st1, T h, T nua, T nub) {
     ps_status st = pass_zcurl(src, mhd);
     if (st) return st;
     const PipeShape ps = pipe_shape(var_of(p, "pipe"));
-    const int slabs = std::min(ps.slabs, b.nz);
+    const int slabs = std::min(p->fixed.count("pipe") ? ps.slabs : default_slabs(mhd), b.nz);
     if (slabs <= 1) {
       if ((st = yxy(mhd, 0, b.nz))) return st;
     } else if (ps.streams == 0) {
@@ -1379,6 +1396,7 @@ ps_status ps_plan_autotune(ps_plan p, const void* state, ps_model m, int reps) {
       // concurrent launches would blur the per-pass timings); the pipeline
       // setting is chosen afterwards on whole right-hand sides
       p->var["pipe"] = 0;
+      p->fixed.insert("pipe");
       // reps launches of variant v of `kind` (kind "pipe": right-hand sides)
       // between two events; ms = their time
       auto time_v = [&](const char* kind, int v, float& ms) -> ps_status {
