@@ -146,7 +146,9 @@ ps_status ps_nonlinear_mhd(ps_plan p, const void *zhat, void *nhat);
  * z* = z + (dt/2) F(z), z <- z + dt F(z*), F = nonlinear term - viscous
  * term (NS: nu |k|^2 u; MHD: |k|^2 ((nu+eta)/2 z+- + (nu-eta)/2 z-+)).
  * One RK2 step is replayed from a captured HIP graph unless graphs are
- * disabled or kernel timing is on.  Needs a workspace. */
+ * disabled or kernel timing is on; the graph is captured behind the first step
+ * that repeats (same state, model and coefficients), which itself is launched
+ * kernel by kernel.  Needs a workspace. */
 ps_status ps_rk2_step(ps_plan p, void *state, ps_model m, double nu, double eta, double dt,
                       int nsteps);
 

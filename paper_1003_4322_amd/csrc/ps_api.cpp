@@ -124,6 +124,7 @@ struct ps_plan_s {
   bool graphs = true;
   hipGraphExec_t gexec = nullptr;
   std::string gkey;
+  std::string ekey;  // key of the last step launched without its graph
   // kernel variants per pass kind (chosen by ps_plan_autotune or by hand)
   std::map<std::string, int> var;
   std::set<std::string> fixed;  // kinds set by the caller or chosen by the tuner
@@ -1139,7 +1140,7 @@ ps_status ps_rk2_step(ps_plan p, void* state, ps_model m, double nu, double eta,
       }
       char key[256];
       snprintf(key, sizeof key, "%p|%d|%.17g|%.17g|%.17g|%p", state, (int)m, nu, eta, dt, p->ws);
-      if (!p->gexec || p->gkey != key) {
+      auto capture = [&]() -> ps_status {
         if (p->gexec) {
           hipGraphExecDestroy(p->gexec);
           p->gexec = nullptr;
@@ -1161,10 +1162,36 @@ ps_status ps_rk2_step(ps_plan p, void* state, ps_model m, double nu, double eta,
           return hip_fail(e, "hipGraphInstantiate");
         }
         p->gkey = key;
+        return PS_OK;
+      };
+      // The first step of a new key is launched kernel by kernel and the graph is
+      // captured behind it, while the GPU works, and only once the step is known
+      // to repeat (more steps in this call, or the same key in the call before):
+      // capturing first held the GPU idle for it.  Slabs on helper streams are
+      // captured first (their fork and join events are not used both ways), and
+      // so is a step for a stream that its owner is capturing.
+      bool ready = p->gexec && p->gkey == key;
+      if (!ready) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        hipError_t e = hipStreamIsCapturing(p->stream, &cs);
+        if (e != hipSuccess) (void)hipGetLastError();
+        if (e != hipSuccess || cs != hipStreamCaptureStatusNone || pipe_shape(var_of(p, "pipe")).streams != 0) {
+          if (ps_status st = capture()) return st;
+          ready = true;
+        }
       }
       for (int i = 0; i < nsteps; ++i) {
-        hipError_t e = hipGraphLaunch(p->gexec, p->stream);
-        if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
+        if (ready) {
+          hipError_t e = hipGraphLaunch(p->gexec, p->stream);
+          if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
+        } else {
+          if (ps_status st = one_step(p->stream)) return st;
+          if (i + 1 < nsteps || p->ekey == key) {
+            if (ps_status st = capture()) return st;
+            ready = true;
+          }
+          p->ekey = key;
+        }
         if ((i + 1) % every == 0 || i + 1 == nsteps)
           if (ps_status st = check(i + 1)) return st;
       }
