@@ -926,7 +926,8 @@ __global__ __launch_bounds__(xpk_slots(MHD, ELS, RB) * TQ) void k_x_prod_pk(XArg
   const int fld = UNI ? __builtin_amdgcn_readfirstlane(c / HB) : c / HB;
   const int pr = c % HB;
   // grid rows of the workgroup: row0 + rb, rb < RB, in boxes of a.rows rows
-  // (one division per workgroup; a.rows >= RB)
+  // (one division per workgroup; a.rows >= RB, or one box, whose end is the
+  // launch's)
   const unsigned rows = (unsigned)a.rows, nrows = (unsigned)(a.rows * a.nb);
   const unsigned row0 = (unsigned)xcd_remap(blockIdx.x, gridDim.x) * RB;
   const unsigned box0 = row0 / rows, loc0 = row0 - box0 * rows;

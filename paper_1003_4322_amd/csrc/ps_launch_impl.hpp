@@ -266,7 +266,9 @@ hipError_t x_prod_pk_v(bool mhd, bool els, XArgs<T> a, hipStream_t s) {
     if constexpr (!X::fits(FI, FO, RB, LP, 163840)) {
       return hipErrorInvalidValue;
     } else {
-      if (a.rows < RB) return hipErrorInvalidValue;  // the kernel assumes a box holds RB rows
+      // the kernel meets one box end at most: boxes hold RB rows, or the launch is
+      // one box (one-plane slabs of 8 rows of 64 points), which ends it
+      if (a.rows < RB && a.nb > 1) return hipErrorInvalidValue;
       const long grid = (a.rows * a.nb + RB - 1) / RB;
       // dealiased input (kx <= (N - 1) / 3): the pruned form skips the slots
       // that hold only zeros or outputs nobody reads
@@ -349,16 +351,15 @@ hipError_t x_prod_n(bool mhd, bool els, int var, XArgs<T> a, hipStream_t s) {
     return pick(var, std::make_integer_sequence<int, NXPROD>{},
                 [&](auto I) { return x_prod_v<T, N, decltype(I)::value>(mhd, els, a, s); });
   } else {
-    // the default of the form; a launch of fewer rows than a workgroup of the
-    // packed form may take (8-row slabs of rows of 64 points) runs the
-    // half-length one
+    // the default of the form (never chosen by the launch's rows: every z-slab
+    // of a box runs the kernel that the whole box would)
     constexpr bool F = sizeof(T) == 4;
     constexpr int I0 = pick_xprod(F, N, false, false), I1 = pick_xprod(F, N, false, true);
     constexpr int I2 = pick_xprod(F, N, true, false), I3 = pick_xprod(F, N, true, true);
-    const int v = a.rows < 16 ? 0 : mhd ? (els ? I3 : I2) : els ? I1 : I0;
+    const int v = mhd ? (els ? I3 : I2) : els ? I1 : I0;
     auto run = [&](auto I) -> hipError_t {
       constexpr int i = decltype(I)::value;
-      if constexpr (i == 0 || i == I0 || i == I1 || i == I2 || i == I3)
+      if constexpr (i == I0 || i == I1 || i == I2 || i == I3)
         return x_prod_v<T, N, i>(mhd, els, a, s);
       else
         return hipErrorInvalidValue;
