@@ -62,33 +62,41 @@ int variant_count(const char* kind, int N, bool mhd) {
 constexpr int FIN_S = 32, FIN_G = 32;  // shells and plane groups of a workgroup
 
 // totals of the per-shell sums part[s Q + q] (one workgroup of FIN_S * FIN_G
-// threads): thread t adds shells t, t + 1024, ..., then a tree over the threads
+// threads): wave q adds the shells of quantity q, a lane's own in order, then
+// the lanes' pairs (value, compensation) in a tree; the other waves find the
+// maximum.  One barrier: a small box's spectrum is a chain of latencies (NS
+// FP64, whole spectra: 32^3 11.1 us, 64^3 15.0; with a tree of all threads and 30
+// barriers, the values alone 11.9 and 16.7, the pairs 12.9 and 17.9).
 template <int Q>
 __device__ void spec_totals(const double* part, const double* pmax, int npm, int nshell, double* totals,
                             double* red) {
-  const int t = threadIdx.x, nt = FIN_S * FIN_G;
-  for (int q = 0; q < 3; ++q) {
-    double v = 0;
-    if (q < Q) {
-      NSum sum{0, 0};
-      for (int s = t; s < nshell; s += nt) nadd(sum, part[(long)s * Q + q]);
-      v = sum.s + sum.c;
-    } else {
-      for (int i = t; i < npm; i += nt) v = fmax(v, pmax[i]);
-    }
-    red[t] = v;
+  constexpr int NT = FIN_S * FIN_G;
+  const int t = threadIdx.x, lane = t % 64, wv = t / 64;
+  if (wv < Q) {
+    NSum v{0, 0};
+#pragma unroll 4
+    for (int s = lane; s < nshell; s += 64) nadd(v, part[(long)s * Q + wv]);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) nadd(v, NSum{__shfl_down(v.s, d, 64), __shfl_down(v.c, d, 64)});
+    if (lane == 0) totals[wv] = v.s + v.c;
+  }
+  if constexpr (Q == 2) {
+    double m = 0;
+    if (wv >= Q)
+      for (int i = t - Q * 64; i < npm; i += NT - Q * 64) m = fmax(m, pmax[i]);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) m = fmax(m, __shfl_down(m, d, 64));
+    if (lane == 0) red[wv] = m;
     __syncthreads();
-    for (int w = nt / 2; w > 0; w >>= 1) {
-      if (t < w) red[t] = q < Q ? red[t] + red[t + w] : fmax(red[t], red[t + w]);
-      __syncthreads();
+    if (t == 0) {
+      for (int w = Q; w < NT / 64; ++w) m = fmax(m, red[w]);
+      totals[2] = m;
     }
-    if (t == 0) totals[q] = red[0];
-    __syncthreads();
   }
 }
 
 // Workgroup b takes the shell blocks b, b + gridDim.x, ...; each thread adds
-// the planes g, g + FIN_G, ... of one shell, then the groups are added in
+// the planes g, g + FIN_G, ... of one shell, then the groups' pairs are added in
 // order.  The sums go to spec and (every q) to the first plane's place in part,
 // which only this workgroup has read; a launch of one workgroup also forms
 // the totals.
@@ -96,7 +104,7 @@ template <int Q>
 __global__ __launch_bounds__(FIN_S* FIN_G) void k_spec_final(double* part, const double* pmax, int npm,
                                                              int nplanes, int nshell, double* spec,
                                                              double* totals) {
-  __shared__ double sh[Q][FIN_G][FIN_S];
+  __shared__ NSum sh[Q][FIN_G][FIN_S];
   const int l = threadIdx.x % FIN_S, g = threadIdx.x / FIN_S;
   const int nblk = (nshell + FIN_S - 1) / FIN_S;
   for (int b = blockIdx.x; b < nblk; b += gridDim.x) {
@@ -109,23 +117,23 @@ __global__ __launch_bounds__(FIN_S* FIN_G) void k_spec_final(double* part, const
 #pragma unroll
         for (int q = 0; q < Q; ++q) nadd(e[q], part[((long)p * nshell + s) * Q + q]);
 #pragma unroll
-    for (int q = 0; q < Q; ++q) sh[q][g][l] = e[q].s + e[q].c;
+    for (int q = 0; q < Q; ++q) sh[q][g][l] = e[q];
     __syncthreads();
     if (g < Q && s < nshell) {
       NSum sum{0, 0};
-      for (int i = 0; i < FIN_G; ++i) nadd(sum, sh[g][i][l]);
+      for (int i = 0; i < min(FIN_G, nplanes); ++i) nadd(sum, sh[g][i][l]);
       const double v = sum.s + sum.c;
       part[(long)s * Q + g] = v;
       if (Q == 3 || g == 0) spec[g * nshell + s] = v;
     }
     __syncthreads();
   }
-  if (gridDim.x == 1) spec_totals<Q>(part, pmax, npm, nshell, totals, &sh[0][0][0]);
+  if (gridDim.x == 1) spec_totals<Q>(part, pmax, npm, nshell, totals, &sh[0][0][0].s);
 }
 template <int Q>
 __global__ __launch_bounds__(FIN_S* FIN_G) void k_spec_totals(const double* part, const double* pmax, int npm,
                                                               int nshell, double* totals) {
-  __shared__ double red[FIN_S * FIN_G];
+  __shared__ double red[FIN_S * FIN_G / 64];
   spec_totals<Q>(part, pmax, npm, nshell, totals, red);
 }
 

@@ -20,7 +20,8 @@ namespace ps {
 // (DPP moves), and the last lane of a run adds it to the shell's
 // Neumaier-compensated sums in LDS.  The waves' partial sums of a shell are
 // added in wave order.  Kernel 2 (k_spec_final) adds the plane pairs: 32
-// groups of planes, each in plane order, then the groups in order.  Every
+// groups of planes, each in plane order, then the groups in order, and the
+// totals from the shells, as compensated pairs throughout.  Every
 // shell's terms are thus added in one fixed order without atomics, so results
 // are bitwise reproducible.
 //   energy (Q = 2): E(s) = 1/2 sum w |f|^2 and Z(s) = 1/2 sum w |k|^2 |f|^2
@@ -33,7 +34,7 @@ namespace ps {
 // moves instead of shuffles through LDS, took the MHD spectrum of a 512^3 FP32
 // state (3.2 GB) from 2.14 to 0.78 ms (4.1 TB/s), the final sums over several
 // workgroups from 0.126 to about 0.01 ms of it; NS 512^3 FP32 1.99 -> 0.42 ms,
-// MHD 384^3 FP64 1.39 -> 0.66 ms, NS 32^3 FP64 18 -> 12 us.
+// MHD 384^3 FP64 1.39 -> 0.66 ms, NS 32^3 FP64 18 -> 11 us.
 // ---------------------------------------------------------------------------
 constexpr int SPEC_ROWS = 8;     // waves per workgroup of k_spec_planes
 constexpr int SPEC_WIN = 64;     // shells per window
@@ -50,6 +51,11 @@ __device__ __forceinline__ void nadd(NSum& a, double x) {
   else
     a.c += (x - t) + a.s;
   a.s = t;
+}
+// another compensated sum
+__device__ __forceinline__ void nadd(NSum& a, const NSum& b) {
+  nadd(a, b.s);
+  a.c += b.c;
 }
 
 template <typename T>
