@@ -258,12 +258,12 @@ ps_status ps_mhd_spectrum(ps_plan p, const void *zhat, double *spec_dev, double 
  * last-level cache; for v = 7..9, 2^(v-3) slabs (16, 32, 64) as two chains,
  * even and odd slabs, on two helper streams, so that the two slabs in flight
  * still fit the last-level cache while each fills the other's launch gaps;
- * 0 = one slab on the plan's stream (ps_plan_autotune chooses among 0 and
- * 4..6, the settings whose launches do not overlap, unless "overlap" is 1).
- * A plan whose "pipe" was neither set nor tuned (it reads as 0) runs one slab,
- * or, unpruned with fields of more than twice the last-level cache, in-order
- * slabs that fit it.  Every setting computes the same step bit for bit.  Kind "overlap"
- * (0 default, 1): whether ps_plan_autotune may also choose the two-chain
+ * 0 = one slab on the plan's stream; 10 = one slab, or, unpruned with fields
+ * of more than twice the last-level cache, as many in-order slabs as make each
+ * fit it.  A plan whose "pipe" was neither set nor tuned (it reads as 0) runs as
+ * with 10.  ps_plan_autotune chooses among 0, 4..6 and 10, the settings whose
+ * launches do not overlap, unless "overlap" is 1.  Every setting computes the
+ * same step bit for bit.  Kind "overlap" (0 default, 1): whether ps_plan_autotune may also choose the two-chain
  * settings 7..9, for a caller who wants the fastest step over per-kernel
  * timings (a launch's duration is no longer its own when two overlap); it
  * changes no arithmetic.  Setting a variant drops a cached graph. */
@@ -275,9 +275,9 @@ int ps_plan_variant_count(ps_plan p, const char *kind);
  * over reps launches on the caller's state for model m, times the variants
  * within 10 % of the fastest again in three interleaved rounds (each keeping
  * its best time, so that clock drift over the sequence does not rank them)
- * and keeps the fastest; then chooses the "pipe" setting (0 or 4..6, and
- * 7..9 when "overlap" is 1) the same way on whole right-hand sides
- * (evaluated in the first RK stage's mode).  Reads
+ * and keeps the fastest; then chooses the "pipe" setting (0, 4..6 or, where
+ * it is not one slab, 10, and 7..9 when "overlap" is 1) the same way on whole
+ * right-hand sides (evaluated in the first RK stage's mode).  Reads
  * state, writes only the workspace; synchronises the plan's stream.  Plan
  * time, like FFT planning, is not part of a step (Sec. 4 leaves planning out
  * of its timings).  When the environment variable PS_TUNE_CACHE names a

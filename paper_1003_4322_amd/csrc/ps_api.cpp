@@ -150,15 +150,16 @@ size_t csize(const ps_plan_s* p) { return p->dtype == PS_F32 ? 8 : 16; }
 const char* const KINDS[] = {"y", "z", "z_curl", "z_epi", "x_prod", "batch", "prune", "form", "pipe", "overlap"};
 // "pipe" variant v: the y / x / y passes run as z-slabs: 2^v slabs over the
 // three helper streams for v = 1..3, 2^v slabs one after another on the plan's
-// stream for v = 4..6, and 2^(v-3) slabs as two chains (even and odd slabs) on
-// two helper streams for v = 7..9
-constexpr int NPIPE = 10, PIPE_SERIAL = 4, PIPE_TWO = 7;
+// stream for v = 4..6, 2^(v-3) slabs as two chains (even and odd slabs) on two
+// helper streams for v = 7..9, and Seq::default_slabs of them in order for v = 10
+constexpr int NPIPE = 11, PIPE_SERIAL = 4, PIPE_TWO = 7, PIPE_AUTO = 10;
 struct PipeShape {
-  int slabs;    // z-slabs (before capping at the box's planes)
+  int slabs;    // z-slabs (before capping at the box's planes); 0: Seq::default_slabs
   int streams;  // 0: in order on the plan's stream; else helper streams
 };
 PipeShape pipe_shape(int v) {
   if (v <= 0) return {1, 0};
+  if (v == PIPE_AUTO) return {0, 0};
   if (v < PIPE_SERIAL) return {1 << v, 3};
   if (v < PIPE_TWO) return {1 << v, 0};
   return {1 << (v - 3), 2};
@@ -459,28 +460,33 @@ struct Seq {
     return st;
   }
 
-  // In-order slabs of the y / x / y passes where nobody has set or tuned "pipe":
-  // as many as leave a slab's widest field set 230 MB, so that its chain finds
-  // its data in the 256 MB last-level cache.  The three passes alone, us at 1
-  // slab / the count chosen / twice that: NS 512^3 FP32 3358 / 2992 / 3078, MHD
-  // 256^3 FP32 878 / 784 / 811, NS 256^3 FP64 908 / 771 / 826; whole steps MHD 256^3
-  // FP32 3549 -> 3353, 48 boxes of MHD 64^3 FP32 3202 -> 2921, NS 1024^3 FP32 107.8
-  // -> 107.0 ms.  Two slabs lose more in launches than they gain (NS 256^3 FP32
-  // 355 / 376, NS 192^3 FP64 289 / 303), and so do pruned boxes of 384^3 (NS FP64
-  // 2204 / 2302): those keep one slab until they are tuned, as do planes that
-  // one kernel takes through all three passes.
+  // In-order slabs of the y / x / y passes where nobody has set or tuned "pipe",
+  // or that is PIPE_AUTO: as many as leave a slab's widest field set 230 MB, so
+  // that its chain finds its data in the 256 MB last-level cache.  The three
+  // passes alone, us at 1 slab / the count chosen / twice that: NS 512^3 FP32 3358
+  // / 2992 / 3078, MHD 256^3 FP32 878 / 784 / 811, NS 256^3 FP64 908 / 771 / 826;
+  // whole steps MHD 256^3 FP32 3549 -> 3353, 48 boxes of MHD 64^3 FP32 3202 -> 2921,
+  // NS 1024^3 FP32 107.8 -> 107.0 ms.  Two slabs lose more in launches than they
+  // gain (NS 256^3 FP32 355 / 376, NS 192^3 FP64 289 / 303), and so do pruned boxes
+  // of 384^3 (NS FP64 2204 / 2302): those keep one slab until they are tuned, as
+  // do planes that one kernel takes through all three passes.
   int default_slabs(bool mhd) const {
     if (p->prune || ps::plane_fits<T>(b.nx, b.ny, mhd, els(mhd), p->prune)) return 1;
     const double fields = (double)std::max(nphys(mhd), nprod(mhd)) * nb * b.ncp * cs();
     const int slabs = (int)std::ceil(fields / 230e6);
     return slabs < 3 ? 1 : slabs;
   }
+  // slabs of a right-hand side
+  int slabs(bool mhd) const {
+    const int n = p->fixed.count("pipe") ? pipe_shape(var_of(p, "pipe")).slabs : 0;
+    return std::min(n > 0 ? n : default_slabs(mhd), b.nz);
+  }
 
   ps_status rhs(const C* src, bool mhd, int mode, C* out, const C* st0, const C* st1, T h, T nua, T nub) {
     ps_status st = pass_zcurl(src, mhd);
     if (st) return st;
     const PipeShape ps = pipe_shape(var_of(p, "pipe"));
-    const int slabs = std::min(p->fixed.count("pipe") ? ps.slabs : default_slabs(mhd), b.nz);
+    const int slabs = this->slabs(mhd);
     if (slabs <= 1) {
       if ((st = yxy(mhd, 0, b.nz))) return st;
     } else if (ps.streams == 0) {
@@ -1419,15 +1425,14 @@ ps_status ps_plan_autotune(ps_plan p, const void* state, ps_model m, int reps) {
       if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
         return fail(PS_ERR_HIP, "hipEventCreate failed");
       ps_status out = PS_OK;
-      // the passes are timed one at a time with the slab pipeline off (its
-      // concurrent launches would blur the per-pass timings); the pipeline
-      // setting is chosen afterwards on whole right-hand sides
-      p->var["pipe"] = 0;
-      p->fixed.insert("pipe");
+      // the passes are timed one at a time, whole (slabs that run concurrently
+      // would blur the per-pass timings); the pipeline setting is chosen
+      // afterwards on whole right-hand sides
       // reps launches of variant v of `kind` (kind "pipe": right-hand sides)
       // between two events; ms = their time
       auto time_v = [&](const char* kind, int v, float& ms) -> ps_status {
         p->var[kind] = v;
+        p->fixed.insert(kind);
         const char* launch = strcmp(kind, "pipe") ? kind : "step";
         ps_status o = PS_OK;
         hipEventRecord(e0, p->stream);
@@ -1457,6 +1462,9 @@ ps_status ps_plan_autotune(ps_plan p, const void* state, ps_model m, int reps) {
               !(var_of(p, "overlap") == 1 && v >= PIPE_TWO))
             continue;
           p->var[kind] = v;
+          p->fixed.insert(kind);
+          // the slabs an untuned plan takes, where they are not one
+          if (!strcmp(kind, "pipe") && v == PIPE_AUTO && q.slabs(mhd) <= 1) continue;
           if ((out = q.tune_launch(strcmp(kind, "pipe") ? kind : "step", st, mhd))) break;  // warm-up
           out = time_v(kind, v, best_ms[v]);
         }
@@ -1470,9 +1478,8 @@ ps_status ps_plan_autotune(ps_plan p, const void* state, ps_model m, int reps) {
             float ms = 0;
             if ((out = time_v(kind, v, ms)) == PS_OK) best_ms[v] = std::min(best_ms[v], ms);
           }
-        p->var[kind] = (int)(std::min_element(best_ms.begin(), best_ms.end()) - best_ms.begin());
-        p->fixed.insert(kind);
         if (out) break;
+        p->var[kind] = (int)(std::min_element(best_ms.begin(), best_ms.end()) - best_ms.begin());
       }
       hipEventDestroy(e0);
       hipEventDestroy(e1);

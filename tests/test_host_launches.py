@@ -36,3 +36,41 @@ for nf in (3, 6):
                     assert len(kernels[-1]) == len(kernels[0]) and kernels[-1] == kernels[0], (nf, f64, prune, form, v)
                 check(L.ps_plan_destroy(h))
 """)
+
+
+def test_tuner_may_choose_the_untuned_slabs(fake):
+    """An unpruned plan takes in-order slabs by itself (NS 256^3 FP64: four); the
+    tuner has that count among its candidates, and the choice can be set and read
+    back.  Launches cost their threads, several times more where a launch exceeds
+    a limit (the cache), and a fixed overhead."""
+    fake_hip.run(fake, """
+def shape(h):
+    F.fake_reset()
+    check(step(h, 3))
+    return [(l[1], l[2]) for l in launches()]
+
+def tuned(limit, slow, overhead, **v):
+    h = plan(256, 3, True, **v)
+    check(L.ps_plan_set_graphs(h, 0))
+    untuned = shape(h)
+    F.fake_cost(limit, slow, overhead)
+    check(L.ps_plan_autotune(h, STATE, 0, 1))
+    F.fake_cost(1e30, 1, 0)
+    return h, untuned, shape(h), L.ps_plan_get_variant(h, b"pipe")
+
+# slabs of a quarter fit, and every launch costs a little: the untuned count is best
+h, untuned, got, pipe = tuned(3e6, 4.0, 0.1)
+assert len(untuned) == 2 * (2 + 3 * 4), len(untuned)
+assert pipe == 10 and len(got) == len(untuned), (pipe, len(got))
+check(L.ps_plan_set_variant(h, b"pipe", 0))
+assert len(shape(h)) == 10
+check(L.ps_plan_set_variant(h, b"pipe", pipe))
+assert len(shape(h)) == len(untuned)
+# nothing to gain from slabs; only smaller ones fit
+assert tuned(1e30, 1.0, 0.1)[3] == 0
+assert tuned(2e5, 9.0, 0.0)[3] in (5, 6)
+# pruned plans run one slab by themselves
+h = plan(256, 3, True, prune=1, pipe=10)
+check(L.ps_plan_set_graphs(h, 0))
+assert len(shape(h)) == 10
+""")
