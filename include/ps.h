@@ -263,10 +263,11 @@ ps_status ps_mhd_spectrum(ps_plan p, const void *zhat, double *spec_dev, double 
  * fit it.  A plan whose "pipe" was neither set nor tuned (it reads as 0) runs as
  * with 10.  ps_plan_autotune chooses among 0, 4..6 and 10, the settings whose
  * launches do not overlap, unless "overlap" is 1.  Every setting computes the
- * same step bit for bit.  Kind "overlap" (0 default, 1): whether ps_plan_autotune may also choose the two-chain
- * settings 7..9, for a caller who wants the fastest step over per-kernel
- * timings (a launch's duration is no longer its own when two overlap); it
- * changes no arithmetic.  Setting a variant drops a cached graph. */
+ * same step bit for bit.  Kind "overlap" (0 default, 1): whether
+ * ps_plan_autotune may also choose the two-chain settings 7..9, for a caller
+ * who wants the fastest step over per-kernel timings (a launch's duration is
+ * no longer its own when two overlap); it changes no arithmetic.  Setting a
+ * variant drops a cached graph. */
 ps_status ps_plan_set_variant(ps_plan p, const char *kind, int variant);
 int ps_plan_get_variant(ps_plan p, const char *kind);
 int ps_plan_variant_count(ps_plan p, const char *kind);
@@ -277,7 +278,8 @@ int ps_plan_variant_count(ps_plan p, const char *kind);
  * its best time, so that clock drift over the sequence does not rank them)
  * and keeps the fastest; then chooses the "pipe" setting (0, 4..6 or, where
  * it is not one slab, 10, and 7..9 when "overlap" is 1) the same way on whole
- * right-hand sides (evaluated in the first RK stage's mode).  Reads
+ * right-hand sides (evaluated in the first RK stage's mode).  A call that fails
+ * leaves the variants as they were.  Reads
  * state, writes only the workspace; synchronises the plan's stream.  Plan
  * time, like FFT planning, is not part of a step (Sec. 4 leaves planning out
  * of its timings).  When the environment variable PS_TUNE_CACHE names a

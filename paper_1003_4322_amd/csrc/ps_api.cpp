@@ -1413,6 +1413,8 @@ ps_status ps_plan_autotune(ps_plan p, const void* state, ps_model m, int reps) {
     int timed = 0;
     const bool timing = p->timing;
     p->timing = false;
+    const auto var0 = p->var;
+    const auto fixed0 = p->fixed;
     ps_status res = by_type(p, [&](auto* tag) -> ps_status {
       using T = std::remove_pointer_t<decltype(tag)>;
       size_t ci = 0;
@@ -1487,6 +1489,10 @@ ps_status ps_plan_autotune(ps_plan p, const void* state, ps_model m, int reps) {
     });
     p->timing = timing;
     p->tune_timed = timed;
+    if (res != PS_OK) {  // nothing was chosen: the plan stays as it was
+      p->var = var0;
+      p->fixed = fixed0;
+    }
     if (p->gexec) {
       hipGraphExecDestroy(p->gexec);
       p->gexec = nullptr;

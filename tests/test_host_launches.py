@@ -74,3 +74,29 @@ h = plan(256, 3, True, prune=1, pipe=10)
 check(L.ps_plan_set_graphs(h, 0))
 assert len(shape(h)) == 10
 """)
+
+
+def test_failed_tuning_leaves_the_plan(fake):
+    """A tuning run that fails at any launch leaves variants and slabs as they were."""
+    fake_hip.run(fake, """
+kinds = [b"y", b"z", b"z_curl", b"z_epi", b"x_prod", b"pipe"]
+h = plan(256, 3, True)
+check(L.ps_plan_set_graphs(h, 0))
+def state():
+    F.fake_reset()
+    check(step(h, 3))
+    return [L.ps_plan_get_variant(h, k) for k in kinds], [l[:3] for l in launches()]
+before = state()
+F.fake_reset()
+g = plan(256, 3, True)
+check(L.ps_plan_autotune(g, STATE, 0, 1))
+total = len(launches())
+assert total > 100
+for n in sorted({0, 1, 10, 60, total - 200, total - 100, total - 1}):
+    F.fake_reset()
+    F.fake_fail_launch(n)
+    assert L.ps_plan_autotune(h, STATE, 0, 1) != 0, n
+    assert state() == before, n
+F.fake_reset()
+check(L.ps_plan_autotune(h, STATE, 0, 1))
+""")
