@@ -148,7 +148,8 @@ ps_status ps_nonlinear_mhd(ps_plan p, const void *zhat, void *nhat);
  * One RK2 step is replayed from a captured HIP graph unless graphs are
  * disabled or kernel timing is on; the graph is captured behind the first step
  * that repeats (same state, model and coefficients), which itself is launched
- * kernel by kernel.  Needs a workspace. */
+ * kernel by kernel, as are the others if that capture fails.  Needs a
+ * workspace. */
 ps_status ps_rk2_step(ps_plan p, void *state, ps_model m, double nu, double eta, double dt,
                       int nsteps);
 

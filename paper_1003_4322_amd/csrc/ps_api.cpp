@@ -1175,7 +1175,9 @@ ps_status ps_rk2_step(ps_plan p, void* state, ps_model m, double nu, double eta,
       // to repeat (more steps in this call, or the same key in the call before):
       // capturing first held the GPU idle for it.  Slabs on helper streams are
       // captured first (their fork and join events are not used both ways), and
-      // so is a step for a stream that its owner is capturing.
+      // so is a step for a stream that its owner is capturing.  A capture that
+      // fails before any step has run fails the call, with the state untouched;
+      // behind a step it only means that the steps go on kernel by kernel.
       bool ready = p->gexec && p->gkey == key;
       if (!ready) {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -1186,15 +1188,21 @@ ps_status ps_rk2_step(ps_plan p, void* state, ps_model m, double nu, double eta,
           ready = true;
         }
       }
+      bool tried = false;
       for (int i = 0; i < nsteps; ++i) {
         if (ready) {
           hipError_t e = hipGraphLaunch(p->gexec, p->stream);
           if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
         } else {
           if (ps_status st = one_step(p->stream)) return st;
-          if (i + 1 < nsteps || p->ekey == key) {
-            if (ps_status st = capture()) return st;
-            ready = true;
+          if (!tried && (i + 1 < nsteps || p->ekey == key)) {
+            tried = true;
+            const std::string detail = g_last_error;
+            ready = capture() == PS_OK;
+            if (!ready) {
+              g_last_error = detail;
+              (void)hipGetLastError();
+            }
           }
           p->ekey = key;
         }

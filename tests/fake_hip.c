@@ -14,7 +14,8 @@ enum { OK = 0, INVALID = 1, OUT_OF_MEMORY = 2, INVALID_CONFIG = 9, MAX_LAUNCHES 
 
 static Launch launches[MAX_LAUNCHES];
 static long nlaunch, nreplay, ninst, fail_begin, fail_end, fail_inst, fail_launch = -1;
-static uint64_t capturing, next_handle = 16;
+static int capturing;
+static uint64_t next_handle = 16;
 static double now_ms, limit_threads = 1e30, slow = 1, overhead_ms;
 static int last_error;
 static D3 cfg_grid, cfg_block;
@@ -53,7 +54,7 @@ int hipLaunchKernel(const void* f, D3 g, D3 b, void** args, size_t shmem, void* 
   /* a launch has fewer than 2^32 threads in all and at most 1024 a workgroup */
   if (blocks == 0 || threads == 0 || threads > 1024 || blocks * threads >= (1ull << 32)) return err(INVALID_CONFIG);
   if (nlaunch >= MAX_LAUNCHES || (fail_launch >= 0 && nlaunch >= fail_launch)) return err(OUT_OF_MEMORY);
-  const int cap = capturing && (uint64_t)(uintptr_t)st == capturing;
+  const int cap = capturing; /* one thread: the capture's stream or one forked from it */
   launches[nlaunch++] = (Launch){f, blocks, threads, (uint64_t)(uintptr_t)st, cap};
   if (!cap) {
     const double t = (double)(blocks * threads);
@@ -91,7 +92,7 @@ int hipEventSynchronize(double* e) { (void)e; return OK; }
 int hipEventElapsedTime(float* ms, double* a, double* b) { *ms = (float)(*b - *a); return OK; }
 
 /* ---- graphs */
-int hipStreamBeginCapture(void* s, int m) { (void)m; if (fail_begin > 0) { --fail_begin; return err(OUT_OF_MEMORY); } capturing = (uint64_t)(uintptr_t)s; return OK; }
+int hipStreamBeginCapture(void* s, int m) { (void)s; (void)m; if (fail_begin > 0) { --fail_begin; return err(OUT_OF_MEMORY); } capturing = 1; return OK; }
 int hipStreamEndCapture(void* s, void** g) {
   (void)s;
   capturing = 0;

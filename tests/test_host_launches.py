@@ -100,3 +100,49 @@ for n in sorted({0, 1, 10, 60, total - 200, total - 100, total - 1}):
 F.fake_reset()
 check(L.ps_plan_autotune(h, STATE, 0, 1))
 """)
+
+
+@pytest.mark.parametrize("where", ["begin", "end", "instantiate"])
+def test_failed_capture_behind_a_step(fake, where):
+    """The graph is captured behind a step that has run: where that fails, the call
+    still takes its steps, kernel by kernel, and a later call captures.  A capture
+    that comes first (slabs on helper streams) fails the call before any launch."""
+    fake_hip.run(fake, f"""
+where = {["begin", "end", "instantiate"].index(where)}
+def fail_once():
+    F.fake_reset()
+    F.fake_fail(*[int(i == where) for i in range(3)])
+def done():
+    return sum(not l[4] for l in launches()), F.fake_replays()
+h = plan(96, 3)
+check(L.ps_plan_set_graphs(h, 0))
+check(step(h, 3))
+per = len(launches())
+check(L.ps_plan_set_graphs(h, 1))
+# several steps in a call; then the capture succeeds behind the next call's first
+fail_once()
+check(step(h, 3, 4))
+assert done() == (4 * per, 0), done()
+assert F.fake_last_error() == 0
+F.fake_reset()
+check(step(h, 3, 3))
+assert done() == (per, 2), done()
+# one-step calls: the second tries to capture
+F.fake_reset()
+check(step(h, 3, 1, state=2 * STATE))
+fail_once()
+check(step(h, 3, 1, state=2 * STATE))
+assert done() == (per, 0), done()
+F.fake_reset()
+check(step(h, 3, 1, state=2 * STATE))
+check(step(h, 3, 1, state=2 * STATE))
+assert done() == (per, 1), done()
+# slabs on helper streams: nothing has run when the call fails
+check(L.ps_plan_set_variant(h, b"pipe", 8))
+fail_once()
+assert step(h, 3, 2) != 0
+assert done() == (0, 0), done()
+F.fake_reset()
+check(step(h, 3, 2))
+assert done() == (0, 2), done()
+""")
