@@ -45,6 +45,19 @@ long z_grid(int ny, int ntile, int nb, bool listed, const DiskTiles* dt, const i
   return (long)ntile * ny * nb;
 }
 
+// f(b0, n) for the boxes [0, nb) in runs [b0, b0 + n) whose launches, of
+// per_box workgroups of nt threads a box, stay below the 2^32 threads a launch
+// may have (one run but for ensembles of millions of small boxes)
+template <class F>
+hipError_t by_launch(int nb, long per_box, int nt, F&& f) {
+  const long most = 0xffffffffL / (per_box * nt);
+  for (long b0 = 0; b0 < nb; b0 += most) {
+    const hipError_t e = f((int)b0, (int)(nb - b0 < most ? nb - b0 : most));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // tile widths a length's z-pass variants use (bit w: width w)
 template <typename T>
 unsigned z_curl_widths(int N);

@@ -72,23 +72,26 @@ template <typename T>
 hipError_t launch_plane(int N, bool mhd, bool els, bool prune, bool many, PlaneArgs<T> a, hipStream_t s) {
   hipError_t r = hipErrorInvalidValue;
   if (a.g.nx != N || a.g.ny != N) return r;
-  const long grid = (long)a.nz * a.nb;
-  if (grid <= 0) return hipSuccess;
+  if (a.nz <= 0 || a.nb <= 0) return hipSuccess;
   plane_pick(N, mhd, els, prune, [&](auto n, auto m, auto e, auto p) {
     constexpr int N_ = decltype(n)::value;
     constexpr bool M_ = decltype(m)::value, E_ = decltype(e)::value, P_ = decltype(p)::value;
     const int k = plane_kernel<T, N_, M_, E_, P_>(many);
+    auto go = [&](auto kernel, int nt) {
+      r = by_launch(a.nb, a.nz, nt, [&](int b0, int nb) {
+        PlaneArgs<T> b = a;
+        b.work += b0 * a.bs;
+        b.nb = nb;
+        kernel<<<dim3((unsigned)((long)a.nz * nb)), dim3(nt), 0, s>>>(b);
+        return hipGetLastError();
+      });
+    };
     if constexpr (plane_kernel<T, N_, M_, E_, P_>(true) == 1) {
-      if (k == 1)
-        k_plane<T, N_, M_, E_, P_>
-            <<<dim3((unsigned)grid), dim3(PlaneCfg<T, N_, M_, E_, P_>::NW * 64), 0, s>>>(a);
+      if (k == 1) go(k_plane<T, N_, M_, E_, P_>, PlaneCfg<T, N_, M_, E_, P_>::NW * 64);
     }
     if constexpr (plane_kernel<T, N_, M_, E_, P_>(false) == 2) {
-      if (k == 2)
-        k_plane_field<T, N_, M_, E_, P_>
-            <<<dim3((unsigned)grid), dim3(PlaneFieldCfg<T, N_, M_, E_, P_>::NW * 64), 0, s>>>(a);
+      if (k == 2) go(k_plane_field<T, N_, M_, E_, P_>, PlaneFieldCfg<T, N_, M_, E_, P_>::NW * 64);
     }
-    r = k ? hipGetLastError() : hipErrorInvalidValue;
   });
   return r;
 }

@@ -32,17 +32,24 @@ bool planefft_fits(int nx, int ny) {
 template <typename T>
 hipError_t launch_planefft(int N, int dir, PlaneFftArgs<T> a, hipStream_t s) {
   hipError_t r = hipErrorInvalidValue;
-  const long grid = (long)a.nz * a.nf * a.nb;
-  if (grid <= 0) return hipSuccess;
+  const long per_box = (long)a.nz * a.nf;
+  if (per_box <= 0 || a.nb <= 0) return hipSuccess;
   planefft_pick(N, [&](auto n) {
-    using P = PlaneFftCfg<T, decltype(n)::value>;
-    if constexpr (P::FITS) {
-      if (dir == INV)
-        k_plane_c2r<T, decltype(n)::value><<<dim3((unsigned)grid), dim3(P::NT), 0, s>>>(a);
-      else
-        k_plane_r2c<T, decltype(n)::value><<<dim3((unsigned)grid), dim3(P::NT), 0, s>>>(a);
-      r = hipGetLastError();
-    }
+    constexpr int N_ = decltype(n)::value;
+    using P = PlaneFftCfg<T, N_>;
+    if constexpr (P::FITS)
+      r = by_launch(a.nb, per_box, P::NT, [&](int b0, int nb) {
+        PlaneFftArgs<T> b = a;
+        b.cplx += b0 * a.bs;
+        b.real += b0 * per_box * N_ * N_;
+        b.nb = nb;
+        const dim3 grid((unsigned)(per_box * nb));
+        if (dir == INV)
+          k_plane_c2r<T, N_><<<grid, dim3(P::NT), 0, s>>>(b);
+        else
+          k_plane_r2c<T, N_><<<grid, dim3(P::NT), 0, s>>>(b);
+        return hipGetLastError();
+      });
   });
   return r;
 }

@@ -146,3 +146,29 @@ F.fake_reset()
 check(step(h, 3, 2))
 assert done() == (0, 2), done()
 """)
+
+
+def test_ensembles_past_one_launch(fake):
+    """A launch holds fewer than 2^32 threads. Ensembles of small boxes whose plane
+    kernels would need more (1.5 million boxes of 8^3, NS 94 GB of FP32 workspace)
+    run them in several launches that take every plane once."""
+    fake_hip.run(fake, """
+for n, nb, nf in ((8, 1500000, 3), (8, 1500000, 6)):
+    h, small = plan([n] * nb, nf), plan([n] * 1000, nf)
+    check(L.ps_plan_set_graphs(h, 0))
+    check(L.ps_plan_set_graphs(small, 0))
+    def blocks(f, *a):
+        F.fake_reset()
+        check(f(*a))
+        n = {}
+        for l in launches():
+            n[l[0]] = n.get(l[0], 0) + l[1]
+        return n
+    for f, a in ((L.ps_fft_r2c, (STATE, 2 * STATE)), (L.ps_fft_c2r, (STATE, 2 * STATE)),
+                 (step, (nf,)), (L.ps_nonlinear_mhd if nf == 6 else L.ps_nonlinear_ns, (STATE, 2 * STATE))):
+        big, ref = blocks(f, h, *a), blocks(f, small, *a)
+        for k, m in big.items():
+            if k in ref:  # (few boxes may run other kernels of a pass)
+                assert m * 1000 == ref[k] * nb, (n, nf, f, m, ref[k])
+    check(L.ps_plan_destroy(h))
+""")
