@@ -156,7 +156,9 @@ def plan_args(header: Dict[str, Any]) -> Dict[str, Any]:
 def apply_variants(plan, header: Dict[str, Any]) -> Dict[str, int]:
     """Set the kernel variants a checkpoint recorded on `plan`; returns them.
     Raises ValueError if the plan's element type, field count or state size
-    differs from the checkpoint's."""
+    differs from the checkpoint's.  "pipe" 0 is what a plan reads that chooses
+    its z-slabs by itself; it is not set on a plan that reads it too, which goes
+    on choosing them (every setting computes the same step bit for bit)."""
     if _DTYPES[plan.complex_dtype] != header["dtype"] or plan.nfields != header["nfields"]:
         raise ValueError(f"plan ({_DTYPES[plan.complex_dtype]}, {plan.nfields} fields) does not match "
                          f"the checkpoint ({header['dtype']}, {header['nfields']} fields)")
@@ -165,5 +167,7 @@ def apply_variants(plan, header: Dict[str, Any]) -> Dict[str, int]:
                          f"{int(np.prod(header['shape']))}")
     v = header.get("variants") or {}
     for kind, value in v.items():
+        if kind == "pipe" and int(value) == 0 and plan.variant(kind) == 0:
+            continue
         plan.set_variant(kind, int(value))
     return dict(v)
