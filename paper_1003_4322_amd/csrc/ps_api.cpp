@@ -63,6 +63,8 @@ struct Class {
   void* twz = nullptr;
   const ps::DiskTiles* dt = nullptr;  // z-pass disk tile lists, owned by the plan
   bool same_grid(int x, int y, int z) const { return nx == x && ny == y && nz == z; }
+  // grid rows in all boxes of the class
+  long rows() const { return (long)nb * ny * nz; }
 };
 
 // length of the axis a pass kind transforms ("z_curl", "z_epi", "z": z;
@@ -196,7 +198,7 @@ void default_variants(ps_plan_s* p) {
                                            {"z", ps::pick_strided(f32, c->nz)},
                                            {"z_curl", ps::pick_zcurl(f32, c->nz, mhd, p->els, p->prune)},
                                            {"z_epi", ps::pick_zepi(f32, c->nz, mhd, p->els)},
-                                           {"x_prod", ps::pick_xprod(f32, c->nx, mhd, p->els)}};
+                                           {"x_prod", ps::pick_xprod(f32, c->nx, mhd, p->els, c->rows())}};
   for (auto& k : d)
     if (!p->fixed.count(k.first) && ps::variant_count(k.first, axis_len(*c, k.first), mhd) > k.second)
       p->var[k.first] = k.second;
@@ -408,7 +410,8 @@ struct Seq {
     // streaming stores once the product rows written exceed the 256 MB
     // last-level cache
     xa.nt = (double)nprod * nb * nz * b.ny * (xa.kmax + 1) * cs() > 268435456.0;
-    const int v = var_of(p, "x_prod");
+    const int v = ps::has_variants(b.nx) ? var_of(p, "x_prod")
+                                        : ps::pick_xprod(sizeof(T) == 4, b.nx, mhd, els(mhd), b.rows());
     const double per = (double)nz / b.nz * (p->prune ? (double)b.nz * b.ny * b.kx_keep : (double)b.nc);
     return enqueue(p, s, "x_prod", (double)(nphys + nprod) * nb * per * cs(),
                    [&](hipStream_t q) { return ps::launch_x_prod<T>(b.nx, mhd, els(mhd), v, xa, q); });

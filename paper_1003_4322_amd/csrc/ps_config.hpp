@@ -209,13 +209,19 @@ constexpr int NXPROD = sizeof(XPROD_V) / sizeof(XV);
 constexpr int pick_strided(bool f32, int n) { return !f32 && n == 384 ? 4 : 5; }
 // Products: the packed form wherever its transforms fill the workgroup (NS:
 // FP32 192 97 -> 69, 256 229 -> 167, 512 1739 -> 1284; FP64 96 31 -> 25, 128 43
-// -> 39, 192 211 -> 141, 256 430 -> 327); with the radix-16 schedule for FP64
-// rows of 384 and more (NS 512 3878 -> 2733) and where twelve FP64 fields leave
-// one workgroup per CU (MHD rotational 192 402 -> 356); the half-length form
+// -> 38, 192 211 -> 141, 256 430 -> 327); with the radix-16 schedule for FP64
+// rows of 384 and more (NS 512 3878 -> 2733); the half-length form
 // for short rows, MHD rotational FP32 at 384 (2237 -> 1570 with two rows; packed
-// 1726) and FP64 at 512 (6282; packed 7179), and beyond 512 where the packed
-// transforms of twelve fields would need more than 1024 threads.
-constexpr int pick_xprod(bool f32, int n, bool mhd, bool els) {
+// 1726) and FP64 at 192 (828, radix 16 packed 874) and 512 (6282; packed 7179), NS
+// divergence form FP64 at 512 (4826; radix 16 packed 5431), and beyond 512 where
+// the packed transforms of twelve fields would need more than 1024 threads.
+// FP64 rows of 128 points by the fields: rotational NS packed radix 16 (128^3 84;
+// radix 8 100, half-length 93), but half-length below 6144 rows; the NS
+// divergence form half-length (81, packed 87) up to 98304 rows (six boxes 534,
+// packed 476); rotational MHD half-length (168; packed 218 and, radix 16, 182), and
+// packed radix 16 from 98304 rows on (six boxes 1025 against 1114); a few hundred
+// rows packed radix 8 everywhere (NS 384 rows 19.5 against 23).
+constexpr int pick_xprod(bool f32, int n, bool mhd, bool els, long rows) {
   const bool rot12 = mhd && !els;
   if (n < 64 || (n == 96 && f32 && els && !mhd)) return 0;
   if (f32) {
@@ -223,8 +229,19 @@ constexpr int pick_xprod(bool f32, int n, bool mhd, bool els) {
     if (n > 512 && rot12) return 8;
     return 18;
   }
-  if (rot12) return n >= 512 ? 7 : n == 192 || n == 256 ? 15 : 18;
-  return n >= 384 && !(n == 512 && els && mhd) ? 15 : 18;
+  if (n == 128 && !(els && mhd)) {
+    if (rows < (mhd ? 1024 : 2048)) return 18;
+    return rows < (mhd || els ? 98304 : 6144) ? 0 : els ? 18 : 15;
+  }
+  if (rot12) return n >= 512 ? 7 : n == 192 ? 0 : n == 256 ? 15 : 18;
+  if (n == 512 && els) return mhd ? 18 : 7;
+  return n >= 384 ? 15 : 18;
+}
+// whether some number of rows has variant i picked
+constexpr bool xprod_picked(bool f32, int n, bool mhd, bool els, int i) {
+  for (long rows : {0L, 4096L, 1L << 40})
+    if (pick_xprod(f32, n, mhd, els, rows) == i) return true;
+  return false;
 }
 // Inverse z + curl: full-width tiles (16 columns in FP32, 8 in FP64) with the
 // radix-16 schedule, MHD in two workgroups per tile (NS FP64 256 471 -> 314, 512

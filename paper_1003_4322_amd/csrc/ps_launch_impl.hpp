@@ -351,22 +351,17 @@ hipError_t x_prod_n(bool mhd, bool els, int var, XArgs<T> a, hipStream_t s) {
     return pick(var, std::make_integer_sequence<int, NXPROD>{},
                 [&](auto I) { return x_prod_v<T, N, decltype(I)::value>(mhd, els, a, s); });
   } else {
-    // the default of the form (never chosen by the launch's rows: every z-slab
-    // of a box runs the kernel that the whole box would)
-    constexpr bool F = sizeof(T) == 4;
-    constexpr int I0 = pick_xprod(F, N, false, false), I1 = pick_xprod(F, N, false, true);
-    constexpr int I2 = pick_xprod(F, N, true, false), I3 = pick_xprod(F, N, true, true);
-    const int v = mhd ? (els ? I3 : I2) : els ? I1 : I0;
-    auto run = [&](auto I) -> hipError_t {
+    // one of those pick_xprod names (for the rows of the class, never of the
+    // launch: every z-slab of a box runs the kernel that the whole box would)
+    return pick(var, std::make_integer_sequence<int, NXPROD>{}, [&](auto I) -> hipError_t {
       constexpr int i = decltype(I)::value;
-      if constexpr (i == I0 || i == I1 || i == I2 || i == I3)
+      constexpr bool F = sizeof(T) == 4;
+      if constexpr (xprod_picked(F, N, false, false, i) || xprod_picked(F, N, false, true, i) ||
+                    xprod_picked(F, N, true, false, i) || xprod_picked(F, N, true, true, i))
         return x_prod_v<T, N, i>(mhd, els, a, s);
       else
         return hipErrorInvalidValue;
-    };
-    return v == 0    ? run(std::integral_constant<int, 0>{})
-           : v == 15 ? run(std::integral_constant<int, 15>{})
-                     : run(std::integral_constant<int, 18>{});
+    });
   }
 }
 

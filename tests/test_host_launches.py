@@ -172,3 +172,19 @@ for n, nb, nf in ((8, 1500000, 3), (8, 1500000, 6)):
                 assert m * 1000 == ref[k] * nb, (n, nf, f, m, ref[k])
     check(L.ps_plan_destroy(h))
 """)
+
+
+# FP64 rows of 128 and 192 points, whose product kernel is chosen by form and rows:
+# workgroups and threads of the launch on one cube
+@pytest.mark.parametrize("n,nf,form,launch", [(128, 6, 0, (8192, 192)), (128, 3, 0, (2048, 192)),
+                                              (128, 3, 1, (4096, 160)), (192, 6, 0, (36864, 144))])
+def test_product_kernel_fp64(fake, n, nf, form, launch):
+    """Rotational MHD and the NS divergence form take the half-length form (one or
+    two rows a workgroup), rotational NS at 128 the packed one in radix 16."""
+    fake_hip.run(fake, f"""
+h = plan({n}, {nf}, True, form={form}, pipe=0)
+check(L.ps_plan_set_graphs(h, 0))
+F.fake_reset()
+check(step(h, {nf}))
+assert launches()[2][1:3] == {launch}, launches()[2]
+""")
