@@ -63,8 +63,9 @@ struct Class {
   void* twz = nullptr;
   const ps::DiskTiles* dt = nullptr;  // z-pass disk tile lists, owned by the plan
   bool same_grid(int x, int y, int z) const { return nx == x && ny == y && nz == z; }
-  // grid rows in all boxes of the class
+  // grid rows, and (kx, ky) columns the z passes transform, in all boxes of the class
   long rows() const { return (long)nb * ny * nz; }
+  long columns(bool prune) const { return (long)nb * (prune ? n_disk : (long)ny * H); }
 };
 
 // length of the axis a pass kind transforms ("z_curl", "z_epi", "z": z;
@@ -194,10 +195,11 @@ void default_variants(ps_plan_s* p) {
     if (!c || k.n3 > c->n3) c = &k;
   if (!c) return;
   const bool f32 = p->dtype == PS_F32, mhd = p->nfields == 6;
+  const long points = c->columns(p->prune) * c->nz;
   const std::pair<const char*, int> d[] = {{"y", ps::pick_strided(f32, c->ny)},
                                            {"z", ps::pick_strided(f32, c->nz)},
-                                           {"z_curl", ps::pick_zcurl(f32, c->nz, mhd, p->els, p->prune)},
-                                           {"z_epi", ps::pick_zepi(f32, c->nz, mhd, p->els)},
+                                           {"z_curl", ps::pick_zcurl(f32, c->nz, mhd, p->els, p->prune, points)},
+                                           {"z_epi", ps::pick_zepi(f32, c->nz, mhd, p->els, p->prune, points)},
                                            {"x_prod", ps::pick_xprod(f32, c->nx, mhd, p->els, c->rows())}};
   for (auto& k : d)
     if (!p->fixed.count(k.first) && ps::variant_count(k.first, axis_len(*c, k.first), mhd) > k.second)
@@ -374,7 +376,7 @@ struct Seq {
   bool els(bool) const { return p->els; }
   int nphys(bool mhd) const { return p->els ? (mhd ? 6 : 3) : (mhd ? 12 : 6); }
   // (kx, ky) columns the z passes transform in all boxes of the class
-  long columns() const { return (long)b.nb * (p->prune ? b.n_disk : (long)b.ny * b.H); }
+  long columns() const { return b.columns(p->prune); }
   int nprod(bool mhd) const { return p->els ? (mhd ? 8 : 5) : (mhd ? 6 : 3); }
 
   ps_status pass_zcurl(const C* src, bool mhd) {
@@ -385,14 +387,16 @@ struct Seq {
     ca.in_bs = st_bs(); ca.out_bs = wk_bs(); ca.nb = nb;
     ca.prune = p->prune;
     ca.sx = (T)p->bs[0]; ca.sy = (T)p->bs[1]; ca.sz = (T)p->bs[2];
-    const int v = var_of(p, "z_curl");
+    const int v = ps::has_variants(b.nz)
+                      ? var_of(p, "z_curl")
+                      : ps::pick_zcurl(sizeof(T) == 4, b.nz, mhd, els(mhd), p->prune, columns() * b.nz);
     const double bytes = p->prune ? ((double)nin * b.n_sphere + (double)nphys * b.n_disk * b.nz) * nb * cs()
                                   : (double)(nin + nphys) * nb * b.nc * cs();
     // streaming stores once the output far exceeds the caches (measured: z_curl
     // at 512^3 FP64 0.82 -> 0.74 ms, FP32 unchanged)
     const double out_bytes = (double)nphys * nb * (p->prune ? (double)b.n_disk * b.nz : (double)b.nc) * cs();
     ca.nt = out_bytes > 268435456.0;
-    if (ps::z_curl_by_field(b.nz, columns()))
+    if (ps::z_curl_by_field(b.nz, columns(), sizeof(T) == 4, mhd, els(mhd)))
       return enqueue(p, s, "z_curl", bytes,
                      [&](hipStream_t q) { return ps::launch_z_curl_field<T>(b.nz, mhd, els(mhd), ca, b.dt, q); });
     return enqueue(p, s, "z_curl", bytes,
@@ -445,7 +449,7 @@ struct Seq {
     if (p->prune)
       bytes = ((double)nprod * b.n_disk * b.nz +
                (mode == 0 ? (double)nst * b.nc : (double)(1 + nrw) * nst * b.n_sphere)) * nb * cs();
-    if (ps::z_epi_by_field(b.nz, columns()))
+    if (ps::z_epi_by_field(b.nz, columns(), sizeof(T) == 4))
       return enqueue(p, s, "z_epi", bytes,
                      [&](hipStream_t q) { return ps::launch_z_epi_field<T>(b.nz, mhd, els(mhd), ea, b.dt, q); });
     return enqueue(p, s, "z_epi", bytes,

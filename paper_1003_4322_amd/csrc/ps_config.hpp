@@ -198,9 +198,11 @@ constexpr int NXPROD = sizeof(XPROD_V) / sizeof(XV);
 
 // The variant each pass runs with by default: where nothing else is compiled
 // (lengths below 256) and on a plan that has been neither tuned nor set.
-// Chosen by the length n of the axis the pass transforms, the type and the form,
-// by timing every variant at every length from 24 to 512 (launch times, us,
-// former default -> this one; "pr": pruned).  Lengths 768 and 1024 follow 512.
+// Chosen by the length n of the axis the pass transforms, the type, the form and
+// the size of the class of boxes (points: columns the z pass transforms times n;
+// rows: grid rows), by timing the variants at every length from 24 to 512, and
+// the candidates named below at 768 and 1024, on boxes of 10^3 to 10^8 points
+// (launch times, us, former default -> this one; "pr": pruned).
 //
 // y and z: twiddles staged in LDS beside the tile, radix-8 schedule, except
 // FP64 at 384, where radix 16 saves a whole exchange of a 98 KB tile (inverse +
@@ -251,8 +253,26 @@ constexpr bool xprod_picked(bool f32, int n, bool mhd, bool els, int i) {
 // at 48 and 64 in FP32, and for pruned FP64 NS at 96 and 192 (44 against 65) the
 // radix-8 schedule, MHD rotational again in two workgroups (FP64 128 113 -> 81;
 // FP32 256 461 -> 430, 512 4016 -> 3704).
-constexpr int pick_zcurl(bool f32, int n, bool mhd, bool els, bool prune) {
+// Few columns leave full-width tiles too few waves: NS boxes of fewer points run
+// half-width tiles with the radix-8 schedule (FP64 256 points, 3456 columns 68 us
+// against 91, at 12672 297 against 256; 512, 1600 columns FP32 40 against 57), in
+// the divergence form, which loads half as much, below a million or so (FP64
+// 384, 360 columns 30 against 33, 4312 88 against 79); below 96 points 32768
+// columns are the line (512 x 384 x 8 MHD FP64, 98688 columns 896 against 313).
+// FP64 columns of 768 fit in 64 KB five at a time, which splits every row's cache
+// lines: four instead (NS 3824 -> 1775; MHD divergence form 4286 -> 2449), but two
+// workgroups a tile while MHD columns are few (rotational 216: 141 -> 85, 1600:
+// 367 -> 308).  MHD at 1024: two workgroups (FP32 rotational)
+// and at 128 (FP64 divergence form) only while columns are few (1024: 216 152 ->
+// 121, 24768 4650 -> 3903; 128: 1600 32 -> 27, 8320 132 -> 103).
+constexpr int pick_zcurl(bool f32, int n, bool mhd, bool els, bool prune, long points) {
   const bool rot12 = mhd && !els;
+  if (n < 96 && points / n <= 32768) return 0;
+  const long few = !els ? (n == 384 ? 3200000 : 2450000) : f32 && n > 192 ? 1500000 : 1000000;
+  if (n >= 96 && !mhd && points < few) return 0;
+  if (n == 768 && !f32) return mhd && points < 1500000 ? 5 : 0;
+  if (n == 1024 && f32 && rot12) return points < 1000000 ? 2 : 0;
+  if (n == 128 && !f32 && mhd && els) return points < 640000 ? 1 : 0;
   if (f32) {
     if (n == 48 || n == 64 || n == 384 || n == 768) return 0;
     if (n == 128) return rot12 ? 1 : mhd ? 5 : 0;
@@ -263,6 +283,13 @@ constexpr int pick_zcurl(bool f32, int n, bool mhd, bool els, bool prune) {
   if (!mhd && (n == 96 || (n == 192 && prune))) return 0;
   return mhd ? 5 : 6;
 }
+// whether some pruning and size have variant i picked
+constexpr bool zcurl_picked(bool f32, int n, bool mhd, bool els, int i) {
+  for (long points : {0L, 800000L, 1200000L, 2000000L, 3000000L, 1L << 40})
+    if (pick_zcurl(f32, n, mhd, els, false, points) == i || pick_zcurl(f32, n, mhd, els, true, points) == i)
+      return true;
+  return false;
+}
 // Forward z + epilogue: full-width tiles with plain register use (NS FP32 256
 // 209 -> 192, 384 pr 333 -> 251, FP64 512 3145 -> 2934); the wide schedule where
 // the accumulators of the Elsasser form or twelve fields crowd the registers
@@ -270,18 +297,28 @@ constexpr int pick_zcurl(bool f32, int n, bool mhd, bool els, bool prune) {
 // 7009); half-width tiles at 192 in FP32 (NS pr 41 -> 29) and for the NS
 // divergence form at 256 and 512; z+ and z- in two workgroups for Elsasser
 // fields at 192 in FP32 (71 -> 65); half-width tiles for
-// rotational MHD at 768 and 1024 (MHD 64 x 96 x 768 FP32, a step: 1262 against
-// 1384 with the wide schedule).
+// MHD at 768 and 1024 (MHD 64 x 96 x 768 FP32, a step: 1262 against 1384 with the
+// wide schedule; Elsasser with z+ and z- in two workgroups, 96 x 384 x 768 FP32
+// pr 829 against 1789, 48 x 64 x 1024 118 against 217).
 // The fields of a tile side by side (12) for MHD at 384 and, Elsasser, 512
-// (k_z_epi_tile's comment has both sides).
-constexpr int pick_zepi(bool f32, int n, bool mhd, bool els) {
+// (k_z_epi_tile's comment has both sides), except where its tiles leave CUs idle
+// (48 x 64 x 512 Elsasser FP32 102 against 156; 48 x 64 x 384 rotational 75
+// against 107, at 16 x 24 columns 71 against 59 for the side-by-side tiles).
+// Half-width tiles, two workgroups a CU, up to 512 where points are few (NS FP32
+// 512 40 -> 46 us with full width, 384 pr up to 4 M points 71 -> 84; FP64 MHD
+// rotational at 384 66 -> 104) and for large boxes of the NS divergence form in
+// FP32 (512^3 pr, two launches, 995 against 1252 with the wide schedule).
+constexpr int pick_zepi(bool f32, int n, bool mhd, bool els, bool prune, long points) {
+  const bool mid = points >= 300000 && points < 1500000;
   if (n < 256) {
     if (mhd && els) return n == 192 ? 5 : 0;
     return f32 && n == 192 ? 1 : !f32 && mhd && n == 96 ? 1 : 0;
   }
-  if (mhd && els) return n == 256 ? (f32 ? 9 : 8) : n <= 512 ? 12 : f32 ? 8 : 9;
-  if (mhd) return n == 384 ? (f32 ? 12 : 0) : n >= 768 ? 5 : n == 512 && !f32 ? 9 : 8;
-  return f32 && els && (n == 256 || n == 512) ? 9 : 0;
+  if (mhd && els) return n == 256 ? (f32 ? 9 : 8) : n >= 768 || (n == 512 && mid) ? 5 : 12;
+  if (mhd && n == 384) return f32 ? (mid ? 5 : 12) : points < 3300000 ? 5 : 0;
+  if (mhd) return n >= 768 ? 5 : n == 512 && !f32 ? 9 : 8;
+  if (f32 && els && n != 384) return n > 512 ? 0 : points < 1000000 || (n == 256 && !prune) ? 9 : 2;
+  return n <= 512 && points < (n != 384 ? 1200000 : !els ? 4000000 : f32 ? 700000 : 1200000) ? 2 : 0;
 }
 
 // Lengths below 256: k_z_epi_tile's groups (0: k_z_epi instead) and columns per

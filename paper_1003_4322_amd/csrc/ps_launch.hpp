@@ -84,20 +84,34 @@ template <typename T>
 hipError_t launch_plane(int N, bool mhd, bool els, bool prune, bool many, PlaneArgs<T> a, hipStream_t s);
 // z passes with the fields of a column tile side by side, for launches whose
 // column tiles alone leave the chip idle; columns: those the pass transforms
-// in all boxes of the launch.  Measured, FP32 pruned / FP64 rotational unpruned
-// unless said (step times, us, one field after another against side by side):
-// the inverse pass gains up to 96 points and 32768 columns (MHD 32^3 FP64 114
-// to 90, NS 96^3 FP64 198 to 192, 16 boxes of 96^3 573 to 564) and loses beyond
-// (200 boxes of 32^3 FP64, 109 k columns, 1557 to 1596; NS 128^3 145 to 146);
+// in all boxes of the class (launch times, us, one field after another against
+// side by side).  The inverse pass gains up to 96 points: for the divergence
+// forms up to 32768 columns (MHD 16 points FP32, 12312 columns 21 to 20, 24768
+// 26 to 27); for the rotational forms, whose fields read their inputs two to
+// four times, as long as these come from the caches: FP64 up to 32768 (512 x 384
+// x 8 MHD 896 to 313; NS from 64 points on to 16384: 64 points, 12800 columns 54 to
+// 49, 25344 119 to 137), FP32 up to 5120 (NS 64 points 4800 columns 25 to 23, 9600
+// 26 to 31; MHD 25344 132 to 238), further where few threads share a column (48
+// points, MHD 24: 14976 columns 93 to 73) and at 96 (NS 24768 columns 87 to 79, MHD
+// 14112 160 to 168).
 constexpr int ZCURL_FIELD_MAXN = 96;
-inline bool z_curl_by_field(int nz, long columns) { return nz <= ZCURL_FIELD_MAXN && columns <= 32768; }
+inline bool z_curl_by_field(int nz, long columns, bool f32, bool mhd, bool els) {
+  if (nz > ZCURL_FIELD_MAXN) return false;
+  if (els) return columns <= 32768;
+  if (!f32) return columns <= (nz >= 64 && !mhd ? 16384 : 32768);
+  if (nz == 48 || (nz == 24 && mhd) || (nz == 96 && !mhd)) return columns <= 32768;
+  return columns <= (nz == 96 ? 16384 : 5120);
+}
 // the epilogue gains at every count up to 64 points (MHD 64^3 103 to 79; 48
 // boxes of 64^3 646 to 611) and up to 128 points while the columns are few
-// (NS 96^3 122 to 104, 1608 columns; NS 96^3 FP64, 4704 columns, 198 to 213; NS
-// 128^3 145 to 135, 2900 columns; unpruned, 8320 columns, 196 to 221).
+// (steps: NS 96^3 122 to 104, 1608 columns; NS 96^3 FP64, 4704 columns, 198 to 213;
+// launches at 128 points: FP32 2903 columns 32 to 25, 3264 40 to 47; FP64 1600 35 to
+// 33, 2496 38 to 48).
 // (48 boxes of NS 64^3: k_z_epi_tile ties with it, 365 us a step; 200 of 32^3:
 // 201 against 194.)
-inline bool z_epi_by_field(int nz, long columns) { return nz <= 64 || (nz <= 128 && columns <= 4096); }
+inline bool z_epi_by_field(int nz, long columns, bool f32) {
+  return nz <= 64 || (nz <= 128 && columns <= (nz == 96 ? 4096 : f32 ? 3000 : 1600));
+}
 template <typename T>
 hipError_t launch_z_curl_field(int N, bool mhd, bool els, ZCurlArgs<T> a, const DiskTiles* dt, hipStream_t s);
 template <typename T>

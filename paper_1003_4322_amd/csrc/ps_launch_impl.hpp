@@ -94,13 +94,16 @@ hipError_t z_curl_m(bool mhd, bool els, ZCurlArgs<T> a, const DiskTiles* dt, hip
   return mhd ? z_curl_v<T, N, I, true>(a, dt, s) : z_curl_v<T, N, I, false>(a, dt, s);
 }
 
-// lengths without variants: the default one
+// lengths without variants: one of those pick_zcurl names
 template <typename T, int N, bool MHD, bool ELS>
-hipError_t z_curl_d(ZCurlArgs<T> a, const DiskTiles* dt, hipStream_t s) {
-  constexpr int whole = pick_zcurl(sizeof(T) == 4, N, MHD, ELS, false);
-  constexpr int pruned = pick_zcurl(sizeof(T) == 4, N, MHD, ELS, true);
-  if (a.prune) return z_curl_v<T, N, pruned, MHD, ELS>(a, dt, s);
-  return z_curl_v<T, N, whole, MHD, ELS>(a, dt, s);
+hipError_t z_curl_d(int var, ZCurlArgs<T> a, const DiskTiles* dt, hipStream_t s) {
+  return pick(var, std::make_integer_sequence<int, NZCURL>{}, [&](auto I) -> hipError_t {
+    constexpr int i = decltype(I)::value;
+    if constexpr (zcurl_picked(sizeof(T) == 4, N, MHD, ELS, i))
+      return z_curl_v<T, N, i, MHD, ELS>(a, dt, s);
+    else
+      return hipErrorInvalidValue;
+  });
 }
 
 template <typename T, int N>
@@ -109,8 +112,8 @@ hipError_t z_curl_n(bool mhd, bool els, int var, ZCurlArgs<T> a, const DiskTiles
     return pick(var, std::make_integer_sequence<int, NZCURL>{},
                 [&](auto I) { return z_curl_m<T, N, decltype(I)::value>(mhd, els, a, dt, s); });
   } else {
-    if (els) return mhd ? z_curl_d<T, N, true, true>(a, dt, s) : z_curl_d<T, N, false, true>(a, dt, s);
-    return mhd ? z_curl_d<T, N, true, false>(a, dt, s) : z_curl_d<T, N, false, false>(a, dt, s);
+    if (els) return mhd ? z_curl_d<T, N, true, true>(var, a, dt, s) : z_curl_d<T, N, false, true>(var, a, dt, s);
+    return mhd ? z_curl_d<T, N, true, false>(var, a, dt, s) : z_curl_d<T, N, false, false>(var, a, dt, s);
   }
 }
 
@@ -198,7 +201,7 @@ hipError_t z_epi_d(ZEpiArgs<T> a, const DiskTiles* dt, hipStream_t s) {
   if constexpr (t.groups != 0)
     return z_epi_tile<T, N, t.tx, LenCfg<N>, MHD, ELS, t.groups>(a, dt, s);
   else
-    return z_epi_v<T, N, pick_zepi(sizeof(T) == 4, N, MHD, ELS), MHD, ELS>(a, dt, s);
+    return z_epi_v<T, N, pick_zepi(sizeof(T) == 4, N, MHD, ELS, false, 0), MHD, ELS>(a, dt, s);
 }
 
 template <typename T, int N>

@@ -8,8 +8,11 @@
 namespace ps {
 
 // Workgroups from which neighbouring tiles go to one XCD (they share cache
-// lines); fewer are spread over all XCDs.
-constexpr unsigned ZREMAP = 2048;
+// lines); fewer are spread over all XCDs.  An inverse pass has several fields'
+// workgroups to a tile, an epilogue one (from 2048 -> from 512, us: MHD 48 x 384 x
+// 64 FP32, 1536 workgroups, 107 -> 53; three boxes of NS 96^3 in the divergence
+// form 117 -> 60; NS 192 x 192 x 128 129 -> 98).
+constexpr unsigned ZREMAP_CURL = 2048, ZREMAP_EPI = 512;
 
 // Inverse z pass + curl (k_z_curl's outputs), one output field per workgroup:
 // the field's inputs are read straight from the state (a base field's one or,
@@ -26,7 +29,7 @@ __global__ __launch_bounds__(TX* TQ) void k_z_curl_field(ZCurlArgs<T> a) {
   __shared__ C2<T> smem[CT::ROWS * TX + L];
   C2<T>* const tws = smem + CT::ROWS * TX;
   const int tid = threadIdx.x, c = tid % TX, q = tid / TX;
-  const int blk = gridDim.x >= ZREMAP ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int blk = gridDim.x >= ZREMAP_CURL ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
   const int fo = blk % NPHYS;
   const Grid& g = a.g;
   const ZTile zt = z_tile(blk / NPHYS, a.ntile, g.ny, a.tiles, a.ntl);
@@ -110,7 +113,7 @@ __global__ __launch_bounds__(NG* TX* TQ) void k_z_epi_field(ZEpiArgs<T> a) {
   C2<T>* const tws = smem + NP * TILE;
   const int tid = threadIdx.x, c = tid % TX, q = tid / TX % TQ, grp = tid / (TX * TQ);
   const Grid& g = a.g;
-  const int blk = gridDim.x >= ZREMAP ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int blk = gridDim.x >= ZREMAP_EPI ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
   const ZTile zt = z_tile(blk, a.ntile, g.ny, a.tiles, a.ntl);
   const int col = zt.tile * TX + c, ky = zt.ky, kyw = wav(ky, g.ny);
   if (a.prune && a.mode != 0 && !g.disk(zt.tile * TX, kyw)) return;
@@ -371,7 +374,7 @@ __global__ __launch_bounds__((EpiTileCfg<T, L, TQ, TX, MHD, ELS, PH>::NT)) void 
   C2<T>* const tws = smem + Cfg::TILES * TILE;
   const int tid = threadIdx.x, c = tid % TX, q = tid / TX % TQ, grp = tid / (TX * TQ);
   const Grid& g = a.g;
-  const int blk = gridDim.x >= ZREMAP ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
+  const int blk = gridDim.x >= ZREMAP_EPI ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x;
   const ZTile zt = z_tile(blk, a.ntile, g.ny, a.tiles, a.ntl);
   const int col = zt.tile * TX + c, ky = zt.ky, kyw = wav(ky, g.ny);
   if (a.prune && a.mode != 0 && !g.disk(zt.tile * TX, kyw)) return;

@@ -47,14 +47,14 @@ hipError_t zfield_pick(int N, bool mhd, bool els, F&& f) {
 }
 
 // Tiles of a field-parallel launch: a launch large enough to be spread over
-// the XCDs tile range by tile range (ZREMAP) takes the pruned tiles from the
+// the XCDs tile range by tile range (from remap on) takes the pruned tiles from the
 // disk list, so that no XCD's range is empty; a small one finds them from its
 // block index, which spares it a dependent load.
 template <int TX>
-long zfield_grid(int ny, int ntile, int nb, int fields, bool pruned, const DiskTiles* dt, const int*& tiles,
-                 int& ntl) {
+long zfield_grid(unsigned remap, int ny, int ntile, int nb, int fields, bool pruned, const DiskTiles* dt,
+                 const int*& tiles, int& ntl) {
   const long all = (long)ntile * ny * nb * fields;
-  if (all >= (long)ZREMAP) return z_grid<TX>(ny, ntile, nb, pruned, dt, tiles, ntl) * fields;
+  if (all >= (long)remap) return z_grid<TX>(ny, ntile, nb, pruned, dt, tiles, ntl) * fields;
   tiles = nullptr;
   ntl = 0;
   return all;
@@ -72,7 +72,7 @@ hipError_t launch_z_curl_field(int N, bool mhd, bool els, ZCurlArgs<T> a, const 
     } else {
       a.ntile = cdiv(a.g.nx / 2 + 1, Z::TXC);
       const long grid =
-          zfield_grid<Z::TXC>(a.g.ny, a.ntile, a.nb, xprod_fin(M_, E_), a.prune != 0, dt, a.tiles, a.ntl);
+          zfield_grid<Z::TXC>(ZREMAP_CURL, a.g.ny, a.ntile, a.nb, xprod_fin(M_, E_), a.prune != 0, dt, a.tiles, a.ntl);
       k_z_curl_field<T, N_, Z::TQ, Z::TXC, typename LenCfg<N_>::RL, M_, E_>
           <<<dim3((unsigned)grid), dim3(Z::TXC * Z::TQ), 0, s>>>(a);
       return hipGetLastError();
@@ -90,7 +90,7 @@ hipError_t launch_z_epi_field(int N, bool mhd, bool els, ZEpiArgs<T> a, const Di
     constexpr int NP = xprod_fout(M_, E_), NG = Z::ng(NP);
     static_assert(Z::epi_lds(NP) <= 163840, "the tile of every product fits in LDS");
     a.ntile = cdiv(a.g.nx / 2 + 1, Z::TXE);
-    const long grid = zfield_grid<Z::TXE>(a.g.ny, a.ntile, a.nb, 1, a.prune && a.mode != 0, dt, a.tiles, a.ntl);
+    const long grid = zfield_grid<Z::TXE>(ZREMAP_EPI, a.g.ny, a.ntile, a.nb, 1, a.prune && a.mode != 0, dt, a.tiles, a.ntl);
     k_z_epi_field<T, N_, Z::TQ, Z::TXE, typename LenCfg<N_>::RL, M_, E_, NG>
         <<<dim3((unsigned)grid), dim3(NG * Z::TXE * Z::TQ), 0, s>>>(a);
     return hipGetLastError();

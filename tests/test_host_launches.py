@@ -188,3 +188,39 @@ F.fake_reset()
 check(step(h, {nf}))
 assert launches()[2][1:3] == {launch}, launches()[2]
 """)
+
+
+# (boxes, fields, FP64, form, prune, pass, variant): each side of the lines of the
+# default variants, where a variant measured at 512 points or on large boxes is
+# the slower one
+@pytest.mark.parametrize("dims,nf,f64,form,prune,kind,want", [
+    ((48, 64, 768), 6, 0, 1, 1, "z_epi", 5), (768, 6, 0, 1, 1, "z_epi", 5), ((96, 384, 768), 6, 1, 1, 0, "z_epi", 5),
+    ((48, 64, 1024), 6, 0, 1, 1, "z_epi", 5), ((16, 24, 1024), 3, 0, 0, 0, "z_epi", 0),
+    ((48, 64, 512), 6, 0, 1, 0, "z_epi", 5), (512, 6, 0, 1, 1, "z_epi", 12),
+    ((48, 64, 384), 6, 0, 0, 0, "z_epi", 5), ((16, 24, 384), 6, 0, 0, 0, "z_epi", 12), (384, 6, 0, 0, 0, "z_epi", 12),
+    ((16, 24, 384), 6, 1, 0, 1, "z_epi", 5), (384, 6, 1, 0, 0, "z_epi", 0),
+    (512, 3, 0, 1, 1, "z_epi", 2), ((16, 24, 512), 3, 0, 1, 1, "z_epi", 9), ((16, 24, 512), 3, 1, 0, 0, "z_epi", 2),
+    ((256, 192, 768), 3, 1, 0, 0, "z_curl", 0), ((256, 192, 768), 6, 1, 1, 0, "z_curl", 0),
+    ((16, 24, 768), 6, 1, 0, 0, "z_curl", 5), ((96, 384, 1024), 6, 0, 0, 0, "z_curl", 0),
+    ((16, 24, 512), 3, 0, 0, 0, "z_curl", 0), (512, 3, 0, 0, 0, "z_curl", 6),
+    ((48, 64, 256), 3, 1, 0, 1, "z_curl", 0), (256, 3, 1, 0, 1, "z_curl", 6),
+])
+def test_default_variants_by_size(fake, dims, nf, f64, form, prune, kind, want):
+    fake_hip.run(fake, f"""
+h = plan({dims}, {nf}, {f64}, form={form}, prune={prune})
+assert L.ps_plan_get_variant(h, b"{kind}") == {want}, L.ps_plan_get_variant(h, b"{kind}")
+""")
+
+
+def test_inverse_z_pass_of_many_columns(fake):
+    """Twelve boxes of MHD 64^3 FP32 have 25344 columns: one field after another (a
+    workgroup for each tile of 8 columns), not one workgroup per field and tile; one
+    box has 2112 and goes field by field."""
+    fake_hip.run(fake, """
+for nb, blocks in ((12, 12 * 64 * 5), (1, 12 * 64 * 5)):
+    h = plan([64] * nb, 6)
+    check(L.ps_plan_set_graphs(h, 0))
+    F.fake_reset()
+    check(step(h, 6))
+    assert launches()[0][1] == blocks, (nb, launches()[0])
+""")
