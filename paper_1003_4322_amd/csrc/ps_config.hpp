@@ -97,7 +97,6 @@ template <typename T, int M, int TQ>
 struct XCfg {
   // LDS slots per row: the larger of the padded and swizzled layouts
   static constexpr int SLOTS = (M + M / 8 + 1) > 32 * (M / 32 + 1) ? (M + M / 8 + 1) : 32 * (M / 32 + 1);
-  static constexpr int G = (256 / TQ) < 1 ? 1 : 256 / TQ;  // plain passes: rows per workgroup
   // lim: LDS bytes per workgroup (64 KB; 80 KB for two workgroups per CU)
   static constexpr bool fits(int f, int rb, int lim = 65536) {
     return (f * rb * SLOTS + 2 * M) * 2 * (int)sizeof(T) <= lim && f * rb * TQ <= 1024;

@@ -7,11 +7,12 @@
 
 namespace ps {
 
-// Schedules per length: Y for the columns; XI / XF for the rows, inverse and
-// forward.  The last radix of XI is the first of XF, so the thread that ends
-// an inverse transform holding points q + TQ b + m (N / R) starts the forward
-// one from the same points, and the products need no exchange.  V8: about
-// eight values per thread; V4: four (more threads, fewer registers).
+// Schedules of the rows per length: XI / XF, inverse and forward.  The last
+// radix of XI is the first of XF, so the thread that ends an inverse transform
+// holding points q + TQ b + m (N / R) starts the forward one from the same
+// points, and the products need no exchange.  V8: about eight values per thread;
+// V4: four (more threads, fewer registers), at 64 points only, where k_plane
+// takes six FP64 fields.
 template <int N>
 struct PlaneLen;
 template <int TQ_, class XI_, class XF_>
@@ -21,19 +22,23 @@ struct PlaneX {
   using XF = XF_;
 };
 #define PS_R(...) Radices<__VA_ARGS__>
-#define PS_PLANE(N_, TQ8, XI8, XF8, TQ4, XI4, XF4) \
-  template <>                                      \
-  struct PlaneLen<N_> {                            \
-    using V8 = PlaneX<TQ8, XI8, XF8>;              \
-    using V4 = PlaneX<TQ4, XI4, XF4>;              \
+#define PS_PLANE(N_, TQ8, XI8, XF8)   \
+  template <>                         \
+  struct PlaneLen<N_> {               \
+    using V8 = PlaneX<TQ8, XI8, XF8>; \
+    using V4 = V8;                    \
   };
-PS_PLANE(8, 1, PS_R(8), PS_R(8), 2, PS_R(2, 4), PS_R(4, 2))
-PS_PLANE(12, 3, PS_R(3, 4), PS_R(4, 3), 3, PS_R(3, 4), PS_R(4, 3))
-PS_PLANE(16, 4, PS_R(4, 4), PS_R(4, 4), 4, PS_R(4, 4), PS_R(4, 4))
-PS_PLANE(24, 3, PS_R(3, 8), PS_R(8, 3), 6, PS_R(3, 2, 4), PS_R(4, 2, 3))
-PS_PLANE(32, 4, PS_R(4, 8), PS_R(8, 4), 8, PS_R(2, 4, 4), PS_R(4, 4, 2))
-PS_PLANE(48, 6, PS_R(3, 4, 4), PS_R(4, 4, 3), 12, PS_R(3, 4, 4), PS_R(4, 4, 3))
-PS_PLANE(64, 8, PS_R(8, 8), PS_R(8, 8), 16, PS_R(4, 4, 4), PS_R(4, 4, 4))
+PS_PLANE(8, 1, PS_R(8), PS_R(8))
+PS_PLANE(12, 3, PS_R(3, 4), PS_R(4, 3))
+PS_PLANE(16, 4, PS_R(4, 4), PS_R(4, 4))
+PS_PLANE(24, 3, PS_R(3, 8), PS_R(8, 3))
+PS_PLANE(32, 4, PS_R(4, 8), PS_R(8, 4))
+PS_PLANE(48, 6, PS_R(3, 4, 4), PS_R(4, 4, 3))
+template <>
+struct PlaneLen<64> {
+  using V8 = PlaneX<8, PS_R(8, 8), PS_R(8, 8)>;
+  using V4 = PlaneX<16, PS_R(4, 4, 4), PS_R(4, 4, 4)>;
+};
 #undef PS_PLANE
 #undef PS_R
 #define PS_FOR_EACH_PLANE_N(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64)
