@@ -4,13 +4,14 @@ them, on either side of each line.
 
 * nx = ny at every length with a plane schedule, nz of another length, pruned
   and not, NS and MHD in both forms, FP32 and FP64: the nonlinear term (which
-  writes zeros outside the sphere) and one RK2 step, rotating in a stretched box.
+  writes zeros outside the sphere) and two RK2 steps, rotating.
 * nx != ny: the three separate passes.
 * Ensembles with fewer and with more planes than CUs, and enough columns for
   the z passes to take the fields one after another.
 
-Tolerances are the shell-wise bars of the parity tests: FP64 1e-12; FP32 5e-5 for
-the nonlinear term and 1e-5 for a step, of the largest value in the shell.
+Tolerances are relative L2 errors over all fields: FP64 1e-12 (2e-12 after the two
+steps); FP32 2e-5 for the nonlinear term, 4e-6 after the two steps and 2e-6 for an
+ensemble's boxes.
 """
 import numpy as np
 import pytest

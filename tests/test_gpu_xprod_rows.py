@@ -1,7 +1,7 @@
 """The packed product pass at the lengths where a wave holds several transforms
 or a transform several waves, on grids with few rows: row counts that are not a
-multiple of a workgroup's, and one-plane slabs of eight rows, which fall back to
-the half-length form.  The nonlinear term against the oracle; the tolerance is
+multiple of a workgroup's, and one-plane slabs of eight rows, fewer than a
+workgroup takes at 64 points.  The nonlinear term against the oracle; the tolerance is
 the parity tests' bar (FP64 1e-12, FP32 2e-5).
 """
 import numpy as np

@@ -1,14 +1,14 @@
-"""The shell-spectrum kernel's enumeration, replayed on the host.
+"""Shell windows of rows, enumerated on the host.
 
-The per-plane spectrum kernel gives each wave a window of 64 consecutive
-shells and R row groups per window, finds in every row the contiguous kx range
-whose shells fall in the window (exact integer bounds), and walks it in chunks
-of 64 modes.  This replays that enumeration with the kernel's integer formulas
-and checks that every mode of every plane is visited exactly once, by the
-window holding its shell, and that the chunks' shells never decrease along the
-lanes (what the segmented scan relies on).  The GPU tests compare the kernel's
-spectra with the oracle; this pins the index bounds on grids whose shell
-counts need one, two and three windows.
+Each wave gets a window of 64 consecutive shells and one of R row groups per
+window, finds in every row the contiguous kx range whose shells fall in the
+window (exact integer bounds), and walks it in chunks of 64 modes.  This checks
+those integer formulas row by row: every mode of every plane is visited exactly
+once, by the window holding its shell, and the chunks' shells never decrease along
+the lanes (what a segmented scan relies on), on grids whose shell counts need
+one, two and three windows.  The spectrum kernel uses the same bounds on row
+orbits (+-ky, +-kz), eight waves to a window; test_spectrum_orbits.py replays its
+walk, and the GPU tests compare its spectra with the oracle.
 """
 import math
 
